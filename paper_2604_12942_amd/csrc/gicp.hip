@@ -6,14 +6,13 @@
 // replaced by 1, 1, 1e-3, the small one on the smallest-scale axis: I - 0.999 a a^T); the target
 // means go into a hashed cell grid of edge slightly above d_corr.
 //
-// Iterate (Gauss-Newton, all on the device, one launch per iteration): sixteen lanes per source
-// Gaussian move its mean by the current pose and find the nearest target mean within d_corr among
-// the 27 neighbouring cells; one lane then forms r = mu_n - q, C = S_n + R S_m R^T, W = C^-1 and
-// J = [-I, [q]x], and accumulates J^T W J, J^T W r, r^T W r and |r|^2 in float64.  Blocks write
-// partials; the block that finishes last adds them in a fixed order, solves the 6x6 system by
-// Cholesky and applies the left update (R, t) <- (Exp(phi) R, Exp(phi) t + rho).  Converged or
-// failed iterations turn the remaining launches into no-ops, so a fixed number of iterations can
-// be queued without host round trips.
+// Iterate (Gauss-Newton, all on the device): sixteen lanes per source Gaussian move its mean by the
+// current pose and find the nearest target mean within d_corr among the 27 neighbouring cells; one
+// lane then forms r = mu_n - q, C = S_n + R S_m R^T, W = C^-1 and J = [-I, [q]x], and accumulates
+// J^T W J, J^T W r, r^T W r and |r|^2 in float64.  Blocks write partials; one block adds them in a
+// fixed order, solves the 6x6 system by Cholesky and applies the left update (R, t) <- (Exp(phi) R,
+// Exp(phi) t + rho).  Converged or failed iterations turn the remaining launches into no-ops, so a
+// fixed number of iterations can be queued without host round trips.
 //
 // The geometric decisions (frustum test, distances, nearest neighbour) use float64 operations
 // rounded one by one in a stated order, so another implementation can reproduce them exactly.
@@ -28,6 +27,7 @@ namespace gsr {
 
 constexpr int kGicpAcc = 30;  // H (21, upper triangle row-major), g (6), cost, |r|^2, count
 enum { kStCost = 27, kStSq = 28, kStCount = 29, kStXi = 30, kStConv = 36, kStIters = 37, kStFailed = 38 };
+constexpr int kGicpSub = 9;         // low key bits: Morton index of the 1/8 cell inside the cell
 constexpr int kGicpChunk = 64;     // sources per block and turn
 constexpr int kGicpBlocks = 2048;  // most blocks of an iteration: eight per CU
 constexpr double kRegSmall = 1e-3;
@@ -99,28 +99,61 @@ __global__ void k_gicp_cov(const uint32_t *__restrict__ list, const uint32_t *__
     cov[5 * cap + j] = 1.0 - k * az * az;
 }
 
+// Smallest box of 16 (and of 256) consecutive target means in grid order.
+struct Box {
+    float4 lo, hi;
+};
+
 // Target means in grid order (x, y, z as float, list position as bits), so that a probe scans a
-// cell's candidates contiguously instead of gathering them through two index arrays.  The first
-// entry of every run of equal hashes also gets the run's end, so that a probe steps through a
-// bucket run by run.
-__global__ void k_gicp_grid_points(const float *__restrict__ means, int64_t n, const uint32_t *__restrict__ tgt_list,
-                                   const uint32_t *__restrict__ counts, const uint32_t *__restrict__ key,
-                                   const uint32_t *__restrict__ val, const uint32_t *__restrict__ bucket,
-                                   float4 *__restrict__ gp, uint32_t *__restrict__ run_end) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)counts[1]) return;
-    const uint32_t p = val[e];
-    const int64_t i = tgt_list[p];
-    gp[e] = make_float4(means[i], means[n + i], means[2 * n + i], __uint_as_float(p));
-    const uint32_t h = key[e];
-    if (e > 0 && key[e - 1] == h) return;
-    uint32_t lo = (uint32_t)e + 1, hi = bucket[(h >> (32 - kBucketBits)) + 1];
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (key[mid] == h) lo = mid + 1;
-        else hi = mid;
+// cell's candidates contiguously instead of gathering them through two index arrays, with the
+// boxes of every 16 and every 256 of them (a block's 256).  The first entry of every cell's run
+// also gets the run's end, so that a probe steps through a bucket run by run.
+__global__ __launch_bounds__(256) void k_gicp_grid_points(
+    const float *__restrict__ means, int64_t n, const uint32_t *__restrict__ tgt_list,
+    const uint32_t *__restrict__ counts, const uint32_t *__restrict__ key, const uint32_t *__restrict__ val,
+    const uint32_t *__restrict__ bucket, float4 *__restrict__ gp, Box *__restrict__ box16, Box *__restrict__ box256,
+    uint32_t *__restrict__ run_end) {
+    __shared__ Box s_box[16];
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, cnt = counts[1];
+    if ((int64_t)blockIdx.x * blockDim.x >= cnt) return;
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (e < cnt) {
+        const uint32_t p = val[e];
+        const int64_t i = tgt_list[p];
+        for (int a = 0; a < 3; a++) v[a] = v[3 + a] = means[a * n + i];
+        gp[e] = make_float4(v[0], v[1], v[2], __uint_as_float(p));
+        const uint32_t h = key[e] >> kGicpSub;
+        if (e == 0 || key[e - 1] >> kGicpSub != h) {
+            uint32_t lo = (uint32_t)e + 1, hi = bucket[(key[e] >> (32 - kBucketBits)) + 1];
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (key[mid] >> kGicpSub == h) lo = mid + 1;
+                else hi = mid;
+            }
+            run_end[e] = lo;
+        }
     }
-    run_end[e] = lo;
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1)
+        for (int a = 0; a < 3; a++) {
+            v[a] = fminf(v[a], __shfl_xor(v[a], off));
+            v[3 + a] = fmaxf(v[3 + a], __shfl_xor(v[3 + a], off));
+        }
+    if ((threadIdx.x & 15) == 0) {
+        const Box b = {make_float4(v[0], v[1], v[2], 0.f), make_float4(v[3], v[4], v[5], 0.f)};
+        s_box[threadIdx.x >> 4] = b;
+        if (e < cnt) box16[e >> 4] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Box b = s_box[0];
+        for (int k = 1; k < 16; k++) {
+            const Box o = s_box[k];
+            b.lo = make_float4(fminf(b.lo.x, o.lo.x), fminf(b.lo.y, o.lo.y), fminf(b.lo.z, o.lo.z), 0.f);
+            b.hi = make_float4(fmaxf(b.hi.x, o.hi.x), fmaxf(b.hi.y, o.hi.y), fmaxf(b.hi.z, o.hi.z), 0.f);
+        }
+        box256[blockIdx.x] = b;
+    }
 }
 
 __device__ __forceinline__ int tri(int i, int j) { return i * 6 - i * (i - 1) / 2 + (j - i); }  // i <= j
@@ -132,9 +165,12 @@ __device__ __forceinline__ bool gicp_stopped(const double *stats) {
 // Nearest target of sixteen lanes' common query q, strictly within sqrt(dd_corr), ties to the
 // lowest list position (0xFFFFFFFF: none).  Every lane looks up two of the 27 cells around q (its
 // own first, then faces, edges and corners), so the dependent loads of the lookups overlap; the
-// lanes then share each cell's candidates.  A cell whose box is farther than the best candidate so
-// far cannot hold a nearer one and is skipped; the box distance is taken a micrometre (and the
-// rounding of the coordinates) short, so that no tie is lost.
+// lanes then share each cell's candidates.  A LiDAR map holds thousands of means in the cells near
+// a sensor, so candidates are tested by boxes of 256, of 16 and one by one (inside a cell they are
+// in Morton order of 1/8 cells, so the boxes are small), starting from the closest box.  What lies
+// farther than the best candidate so far is skipped.  A box's distance is computed with the same
+// rounded operations as its candidates' and each is monotone, so it never exceeds theirs; a cell's
+// is taken a micrometre (and the rounding of the coordinates) short.  No tie is lost.
 __constant__ int8_t kCellOrder[27][3] = {
     {0, 0, 0},   {-1, 0, 0},  {1, 0, 0},   {0, -1, 0},  {0, 1, 0},   {0, 0, -1},  {0, 0, 1},   {-1, -1, 0}, {1, -1, 0},
     {-1, 1, 0},  {1, 1, 0},   {-1, 0, -1}, {1, 0, -1},  {-1, 0, 1},  {1, 0, 1},   {0, -1, -1}, {0, 1, -1},  {0, -1, 1},
@@ -143,6 +179,7 @@ __constant__ int8_t kCellOrder[27][3] = {
 struct GicpGrid {
     const uint32_t *key, *bucket, *run_end;
     const float4 *gp;
+    const Box *box16, *box256;
     double cell, inv_cell;
 };
 
@@ -151,8 +188,88 @@ __device__ __forceinline__ double box_gap(int o, double x, int64_t c, double cel
     return o == 0 || !(g > slack) ? 0.0 : g - slack;
 }
 
+// squared distance of q to a box (0 inside), the operations of sqdist_rn
+__device__ __forceinline__ double box_sqdist(const Box *__restrict__ p, const double q[3]) {
+    const Box b = *p;
+    const double dx = fmax(fmax(__dsub_rn(b.lo.x, q[0]), __dsub_rn(q[0], b.hi.x)), 0.0);
+    const double dy = fmax(fmax(__dsub_rn(b.lo.y, q[1]), __dsub_rn(q[1], b.hi.y)), 0.0);
+    const double dz = fmax(fmax(__dsub_rn(b.lo.z, q[2]), __dsub_rn(q[2], b.hi.z)), 0.0);
+    return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
+}
+
+// One query's search state, the same in its sixteen lanes but for (best, bi) between two merges.
+struct Nearest {
+    const GicpGrid &g;
+    const double *q;
+    double best;
+    uint32_t bi;
+    int sub, sh;  // lane in the group, the group's first lane in the wave
+
+    __device__ __forceinline__ uint32_t group(bool v) const { return (uint32_t)(__ballot(v) >> sh) & 0xFFFFu; }
+    __device__ __forceinline__ void test(uint32_t i) {
+        const float4 a = g.gp[i];
+        const double d = sqdist_rn(a.x, a.y, a.z, q[0], q[1], q[2]);
+        const uint32_t p = __float_as_uint(a.w);
+        if (d < best || (d == best && p < bi && bi != 0xFFFFFFFFu)) best = d, bi = p;
+    }
+    __device__ __forceinline__ void merge() {
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) {
+            const double ob = __shfl_xor(best, off);
+            const uint32_t oi = __shfl_xor(bi, off);
+            if (ob < best || (ob == best && oi < bi)) best = ob, bi = oi;
+        }
+    }
+    // the closest of the boxes [b, e), the first on ties
+    __device__ __forceinline__ uint32_t closest(const Box *__restrict__ boxes, uint32_t b, uint32_t e) const {
+        double d = INFINITY;
+        uint32_t at = b;
+        for (uint32_t k = b + sub; k < e; k += 16) {
+            const double dk = box_sqdist(boxes + k, q);
+            if (dk < d) d = dk, at = k;
+        }
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) {
+            const double od = __shfl_xor(d, off);
+            const uint32_t oa = __shfl_xor(at, off);
+            if (od < d || (od == d && oa < at)) d = od, at = oa;
+        }
+        return at;
+    }
+    // candidates [s, e) of one cell
+    __device__ __forceinline__ void cell(uint32_t s, uint32_t e) {
+        if (e - s <= 64) {
+            for (uint32_t i = s + sub; i < e; i += 16) test(i);
+            merge();
+            return;
+        }
+        const uint32_t b0 = s >> 4, b1 = ((e - 1) >> 4) + 1, c1 = ((e - 1) >> 8) + 1;
+        if (bi == 0xFFFFFFFFu) {  // a first bound from the closest box of the closest 256
+            const uint32_t c = closest(g.box256, s >> 8, c1);
+            const uint32_t k = closest(g.box16, max(c * 16, b0), min(c * 16 + 16, b1)) * 16 + sub;
+            if (k >= s && k < e) test(k);
+            merge();
+        }
+        for (uint32_t c = s >> 8; c < c1; c += 16) {
+            uint32_t open = group(c + sub < c1 && box_sqdist(g.box256 + min(c + sub, c1 - 1), q) <= best);
+            while (open) {
+                const uint32_t b = (c + __builtin_ctz(open)) * 16 + sub;
+                open &= open - 1;
+                uint32_t hit = group(b >= b0 && b < b1 && box_sqdist(g.box16 + min(max(b, b0), b1 - 1), q) <= best);
+                if (!hit) continue;
+                while (hit) {
+                    const uint32_t k = (b - sub + __builtin_ctz(hit)) * 16 + sub;
+                    hit &= hit - 1;
+                    if (k >= s && k < e) test(k);
+                }
+                merge();
+            }
+        }
+    }
+};
+
 __device__ __forceinline__ uint32_t gicp_nearest(const double q[3], const GicpGrid &g, double dd_corr) {
-    const int lane = lane_id(), sub = lane & 15;
+    const int lane = lane_id(), sub = lane & 15, sh = lane & 48;
     const int64_t c[3] = {cell_of(q[0], g.inv_cell), cell_of(q[1], g.inv_cell), cell_of(q[2], g.inv_cell)};
     const double slack = 1e-6 + 1e-12 * fmax(fabs(q[0]), fmax(fabs(q[1]), fabs(q[2])));
     uint32_t first[2], last[2];
@@ -164,46 +281,29 @@ __device__ __forceinline__ uint32_t gicp_nearest(const double q[3], const GicpGr
         gap[k] = 0.f;
         if (slot < 27) {
             const int o0 = kCellOrder[slot][0], o1 = kCellOrder[slot][1], o2 = kCellOrder[slot][2];
-            const uint32_t h = cell_hash(c[0] + o0, c[1] + o1, c[2] + o2);
-            const uint32_t b = h >> (32 - kBucketBits);
-            uint32_t e = g.bucket[b];
-            const uint32_t hi = g.bucket[b + 1];
-            while (e < hi && g.key[e] < h) e = g.run_end[e];
-            if (e < hi && g.key[e] == h) first[k] = e, last[k] = g.run_end[e];
+            const uint32_t hash = cell_hash(c[0] + o0, c[1] + o1, c[2] + o2), h = hash >> kGicpSub;
+            uint32_t e = g.bucket[hash >> (32 - kBucketBits)];
+            const uint32_t hi = g.bucket[(hash >> (32 - kBucketBits)) + 1];
+            while (e < hi && g.key[e] >> kGicpSub < h) e = g.run_end[e];
+            if (e < hi && g.key[e] >> kGicpSub == h) first[k] = e, last[k] = g.run_end[e];
             const double gx = box_gap(o0, q[0], c[0], g.cell, slack), gy = box_gap(o1, q[1], c[1], g.cell, slack),
                          gz = box_gap(o2, q[2], c[2], g.cell, slack);
             gap[k] = (float)((gx * gx + gy * gy + gz * gz) * (1.0 - 1e-6));
         }
     }
-    const int sh = lane & 48;
-    uint32_t cells = (uint32_t)((__ballot(last[0] > first[0]) >> sh) & 0xFFFFull) |
-                     ((uint32_t)((__ballot(last[1] > first[1]) >> sh) & 0xFFFFull) << 16);
-    double best = dd_corr;
-    uint32_t bi = 0xFFFFFFFFu;
-    while (cells) {  // one of at most 27 bits is cleared per turn
+    Nearest s{g, q, dd_corr, 0xFFFFFFFFu, sub, sh};
+    // the nearest-first cells that are not empty, not visited and not farther than the best so far
+    uint32_t left = 0x7FFFFFFu;
+    for (;;) {  // every turn clears at least one of the 27 bits
+        const uint32_t cells = (s.group(last[0] > first[0] && (double)gap[0] <= s.best) |
+                                s.group(last[1] > first[1] && (double)gap[1] <= s.best) << 16) & left;
+        if (!cells) break;
         const int k = __builtin_ctz(cells);
-        cells &= cells - 1;
+        left &= ~0u << k << 1;
         const int from = sh | (k & 15);
-        const uint32_t s = __shfl(k < 16 ? first[0] : first[1], from);
-        const uint32_t e = __shfl(k < 16 ? last[0] : last[1], from);
-        if ((double)__shfl(k < 16 ? gap[0] : gap[1], from) > best) continue;
-        for (uint32_t i = s + sub; i < e; i += 32) {
-            const bool two = i + 16 < e;
-            const float4 a = g.gp[i], b = g.gp[two ? i + 16 : i];
-            const double da = sqdist_rn(a.x, a.y, a.z, q[0], q[1], q[2]);
-            const double db = sqdist_rn(b.x, b.y, b.z, q[0], q[1], q[2]);
-            const uint32_t pa = __float_as_uint(a.w), pb = __float_as_uint(b.w);
-            if (da < best || (da == best && pa < bi && bi != 0xFFFFFFFFu)) best = da, bi = pa;
-            if (db < best || (db == best && pb < bi && bi != 0xFFFFFFFFu)) best = db, bi = pb;
-        }
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-            const double ob = __shfl_xor(best, off);
-            const uint32_t oi = __shfl_xor(bi, off);
-            if (ob < best || (ob == best && oi < bi)) best = ob, bi = oi;
-        }
+        s.cell(__shfl(k < 16 ? first[0] : first[1], from), __shfl(k < 16 ? last[0] : last[1], from));
     }
-    return bi;
+    return s.bi;
 }
 
 // Adds the 64 pairs of a wave (lane = source position j, bi = its target position or none) to
@@ -281,8 +381,6 @@ __device__ __forceinline__ void gicp_pair_sums(uint32_t bi, int64_t j, const flo
     }
 }
 
-__device__ void gicp_solve(const double *s, double *__restrict__ pose, double *__restrict__ stats);
-
 // One Gauss-Newton iteration.  Each block takes chunks of 64 sources: four passes of sixteen
 // sixteen-lane searches, then its first wave linearises the 64 pairs.  The per-block sums go to
 // partial[e][block]; the last of the active blocks adds them and updates the pose.
@@ -291,21 +389,18 @@ __device__ void gicp_solve(const double *s, double *__restrict__ pose, double *_
 // source walked 27 cells and every candidate in them one after another, 1.1 waves per SIMD, in 1.46
 // ms per iteration at 75k sources and 240k targets, and the sum of 5,859 partials (mostly of empty
 // blocks) took another 0.2 ms.
-__global__ __launch_bounds__(256) void k_gicp_iterate(
+__global__ __launch_bounds__(256) void k_gicp_linearise(
     const float *__restrict__ means, int64_t n, const uint32_t *__restrict__ src_list,
     const uint32_t *__restrict__ tgt_list, const uint32_t *__restrict__ counts, const double *__restrict__ src_cov,
-    const double *__restrict__ tgt_cov, int64_t cap, GicpGrid grid, double dd_corr, double *__restrict__ pose,
-    double *__restrict__ stats, double *__restrict__ partial, uint32_t *__restrict__ done,
+    const double *__restrict__ tgt_cov, int64_t cap, GicpGrid grid, double dd_corr,
+    const double *__restrict__ pose, const double *__restrict__ stats, double *__restrict__ partial,
     int32_t *__restrict__ corr) {
     __shared__ uint32_t s_hit[kGicpChunk];
     __shared__ double s_sum[kGicpAcc];
-    __shared__ uint32_t s_last;
     if (gicp_stopped(stats)) return;
     const int64_t n_src = counts[0];
     const int64_t chunks = (n_src + kGicpChunk - 1) / kGicpChunk;
-    // blocks without a chunk are not counted; without any source block 0 reports the failure
-    const uint32_t active = chunks < 1 ? 1u : (chunks < (int64_t)gridDim.x ? (uint32_t)chunks : gridDim.x);
-    if (blockIdx.x >= active) return;
+    if (blockIdx.x >= chunks) return;
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     double R[9], tr[3];
     for (int e = 0; e < 9; e++) R[e] = pose[e];
@@ -314,7 +409,7 @@ __global__ __launch_bounds__(256) void k_gicp_iterate(
     for (int64_t ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
         for (int p = 0; p < kGicpChunk / 16; p++) {
             const int slot = p * 16 + (t >> 4);
-            const int64_t j = ch * kGicpChunk + slot;
+            const int64_t j = slot * chunks + ch;
             uint32_t bi = 0xFFFFFFFFu;
             if (j < n_src) {
                 const int64_t i = src_list[j];
@@ -329,33 +424,12 @@ __global__ __launch_bounds__(256) void k_gicp_iterate(
         }
         __syncthreads();
         if (w == 0) {
-            const int64_t j = ch * kGicpChunk + lane;
+            const int64_t j = lane * chunks + ch;
             gicp_pair_sums(s_hit[lane], j, means, n, src_list, tgt_list, src_cov, tgt_cov, cap, R, tr, s_sum);
         }
         __syncthreads();
     }
     if (w == 0 && lane < kGicpAcc) partial[(int64_t)lane * kGicpBlocks + blockIdx.x] = s_sum[lane];
-    // release the block's sums, then count it; the block that completes the count acquires all sums
-    __threadfence();
-    __syncthreads();
-    if (t == 0) {
-        s_last = atomicAdd(done, 1u) + 1u == active ? 1u : 0u;
-        __threadfence();
-    }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    for (int e = w; e < kGicpAcc; e += 4) {
-        double a = 0.0;
-        for (uint32_t b = lane; b < active; b += 64) a += partial[(int64_t)e * kGicpBlocks + b];
-        a = wave_sum_d(a);
-        if (lane == 0) s_sum[e] = a;
-    }
-    __syncthreads();
-    if (t < kGicpAcc) stats[t] = s_sum[t];
-    if (t != 0) return;
-    *done = 0;
-    gicp_solve(s_sum, pose, stats);
 }
 
 __device__ void so3_exp(const double phi[3], double E[9]) {
@@ -374,8 +448,27 @@ __device__ void so3_exp(const double phi[3], double E[9]) {
         }
 }
 
-// Gauss-Newton update of the pose from the 30 sums (one lane).
-__device__ void gicp_solve(const double *s, double *__restrict__ pose, double *__restrict__ stats) {
+// Fixed-order sum of the active blocks' partials, then the Gauss-Newton update of the pose (one
+// block).  A launch of its own: counting the blocks off inside the iteration's kernel cost every
+// block a write-back of its XCD's L2 (__threadfence), 65 us per iteration more than this launch.
+__global__ __launch_bounds__(1024) void k_gicp_solve(const double *__restrict__ partial,
+                                                     const uint32_t *__restrict__ counts, int grid,
+                                                     double *__restrict__ pose, double *__restrict__ stats) {
+    __shared__ double s[kGicpAcc];
+    if (gicp_stopped(stats)) return;
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int64_t chunks = ((int64_t)counts[0] + kGicpChunk - 1) / kGicpChunk;
+    const int active = chunks < grid ? (int)chunks : grid;
+    for (int e = w; e < kGicpAcc; e += 16) {
+        double a = 0.0;
+#pragma unroll 4
+        for (int b = lane; b < active; b += 64) a += partial[(int64_t)e * kGicpBlocks + b];
+        a = wave_sum_d(a);
+        if (lane == 0) s[e] = a;
+    }
+    __syncthreads();
+    if (t < kGicpAcc) stats[t] = s[t];
+    if (t != 0) return;
     stats[kStIters] += 1.0;
     if (s[kStCount] < 6.0) {
         stats[kStFailed] = 1.0;
@@ -428,7 +521,8 @@ size_t a256g(size_t b) { return (b + 255) & ~(size_t)255; }
 struct GicpWs {
     double *src_cov, *tgt_cov, *partial;
     float4 *gp;
-    uint32_t *f_src, *f_tgt, *off, *key, *val, *k2, *v2, *bucket, *done;
+    Box *box16, *box256;
+    uint32_t *f_src, *f_tgt, *off, *key, *val, *k2, *v2, *bucket;
     void *scan, *sort;
     size_t bytes;
 };
@@ -448,8 +542,9 @@ GicpWs gicp_layout(void *base, int64_t n) {
     w.src_cov = (double *)take(6 * nn * 8);
     w.tgt_cov = (double *)take(6 * nn * 8);
     w.partial = (double *)take((size_t)kGicpBlocks * kGicpAcc * 8);
-    w.done = (uint32_t *)take(4);
     w.gp = (float4 *)take(nn * 16);
+    w.box16 = (Box *)take((nn / 16 + 1) * sizeof(Box));
+    w.box256 = (Box *)take((nn / 256 + 1) * sizeof(Box));
     w.f_src = (uint32_t *)take(nn * 4);
     w.f_tgt = (uint32_t *)take(nn * 4);
     w.off = (uint32_t *)take(nn * 4);
@@ -492,11 +587,12 @@ extern "C" gsr_status gsr_gicp_prepare_launch(const gsr_gaussians *g, const int3
     k_gicp_cov<<<nblk256(n), 256, 0, st>>>(src_index, counts, n, g->quats, g->log_scales, n, w.src_cov);
     k_gicp_cov<<<nblk256(n), 256, 0, st>>>(tgt_index, counts + 1, n, g->quats, g->log_scales, n, w.tgt_cov);
     s = gsr_grid_build_launch(g->means, n, tgt_index, counts + 1, n, grid_cell(d_corr), w.key, w.val, w.k2, w.v2,
-                              w.bucket, w.sort, st);
+                              w.bucket, w.sort, kGicpSub, st);
     if (s != GSR_OK) return s;
     // the sort's second key buffer is free again: it takes the run ends
-    k_gicp_grid_points<<<nblk256(n), 256, 0, st>>>(g->means, n, tgt_index, counts, w.key, w.val, w.bucket, w.gp, w.k2);
-    return gsr_fill_u32_launch(w.done, 0u, 1, st);
+    k_gicp_grid_points<<<nblk256(n), 256, 0, st>>>(g->means, n, tgt_index, counts, w.key, w.val, w.bucket, w.gp,
+                                                   w.box16, w.box256, w.k2);
+    return last_launch();
 }
 
 extern "C" gsr_status gsr_gicp_iterate_launch(const gsr_gaussians *g, const uint32_t *src_index,
@@ -507,12 +603,14 @@ extern "C" gsr_status gsr_gicp_iterate_launch(const gsr_gaussians *g, const uint
     if (n == 0) return GSR_OK;
     GicpWs w = gicp_layout(ws, n);
     const double dd = (double)d_corr * (double)d_corr;
-    const GicpGrid grid = {w.key, w.bucket, w.k2, w.gp, grid_cell(d_corr), 1.0 / grid_cell(d_corr)};
+    const GicpGrid grid = {w.key, w.bucket, w.k2, w.gp, w.box16, w.box256, grid_cell(d_corr), 1.0 / grid_cell(d_corr)};
     const int64_t chunks = ceil_div(n, kGicpChunk);
     const int nb = (int)(chunks < kGicpBlocks ? chunks : kGicpBlocks);
-    for (int it = 0; it < n_iter; it++)
-        k_gicp_iterate<<<nb, 256, 0, st>>>(g->means, n, src_index, tgt_index, counts, w.src_cov, w.tgt_cov, n, grid, dd,
-                                           pose, stats, w.partial, w.done, corr);
+    for (int it = 0; it < n_iter; it++) {
+        k_gicp_linearise<<<nb, 256, 0, st>>>(g->means, n, src_index, tgt_index, counts, w.src_cov, w.tgt_cov, n, grid,
+                                             dd, pose, stats, w.partial, corr);
+        k_gicp_solve<<<1, 1024, 0, st>>>(w.partial, counts, nb, pose, stats);
+    }
     return last_launch();
 }
 

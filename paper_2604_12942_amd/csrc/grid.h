@@ -49,9 +49,12 @@ __device__ __forceinline__ double sqdist_rn(double ax, double ay, double az, dou
 
 // Builds the grid over the points means[c * stride + (index ? index[j] : j)], j < count (count
 // read on the device when count_dev is given, else cap): keys / vals (= j) sorted by hash, and
-// bucket [kBuckets + 1].  k2 / v2 are ping-pong buffers of cap words; sort_ws holds
+// bucket [kBuckets + 1].  The hash's low sub_bits (a multiple of 3, at most 15) are replaced by the
+// Morton index of the 1 / 2^(sub_bits / 3) cell inside the point's cell, which orders a cell's
+// points in space; two cells then share a run when the remaining hash bits agree, as with any
+// other collision.  k2 / v2 are ping-pong buffers of cap words; sort_ws holds
 // gsr_sort_pairs_ws_bytes(cap) bytes.
 extern "C" gsr_status gsr_grid_build_launch(const float *means, int64_t stride, const uint32_t *index,
                                             const uint32_t *count_dev, int64_t cap, double cell, uint32_t *keys,
                                             uint32_t *vals, uint32_t *k2, uint32_t *v2, uint32_t *bucket,
-                                            void *sort_ws, hipStream_t st);
+                                            void *sort_ws, int sub_bits, hipStream_t st);

@@ -101,14 +101,23 @@ __global__ __launch_bounds__(256) void k_gather_rows(RowGroupsDev G, int total_c
 
 // ---- grid over points (the insertion filter's map, the registration's target set) -------------
 __global__ void k_grid_cells(const float *__restrict__ means, int64_t stride, const uint32_t *__restrict__ index,
-                             const uint32_t *__restrict__ count_dev, int64_t cap, double inv_cell,
+                             const uint32_t *__restrict__ count_dev, int64_t cap, double inv_cell, int sub_bits,
                              uint32_t *__restrict__ key, uint32_t *__restrict__ val) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n = count_dev ? (int64_t)*count_dev : cap;
     if (j >= n || j >= cap) return;
     const int64_t i = index ? (int64_t)index[j] : j;
-    key[j] = cell_hash(cell_of(means[i], inv_cell), cell_of(means[stride + i], inv_cell),
-                       cell_of(means[2 * stride + i], inv_cell));
+    int64_t c[3];
+    uint32_t sub = 0;
+    const int axis_bits = sub_bits / 3;
+    for (int a = 0; a < 3; a++) {
+        const double x = (double)means[a * stride + i] * inv_cell;
+        c[a] = (int64_t)floor(x);
+        const int s = (int)((x - floor(x)) * (double)(1 << axis_bits));
+        const int k = s < 0 ? 0 : (s < (1 << axis_bits) ? s : (1 << axis_bits) - 1);
+        for (int b = 0; b < axis_bits; b++) sub |= ((uint32_t)(k >> b) & 1u) << (3 * b + a);
+    }
+    key[j] = (cell_hash(c[0], c[1], c[2]) >> sub_bits << sub_bits) | sub;
     val[j] = (uint32_t)j;
 }
 
@@ -327,9 +336,10 @@ using namespace gsr;
 extern "C" gsr_status gsr_grid_build_launch(const float *means, int64_t stride, const uint32_t *index,
                                             const uint32_t *count_dev, int64_t cap, double cell, uint32_t *keys,
                                             uint32_t *vals, uint32_t *k2, uint32_t *v2, uint32_t *bucket,
-                                            void *sort_ws, hipStream_t st) {
+                                            void *sort_ws, int sub_bits, hipStream_t st) {
     if (cap > 0) {
-        k_grid_cells<<<nblk(cap), 256, 0, st>>>(means, stride, index, count_dev, cap, 1.0 / cell, keys, vals);
+        k_grid_cells<<<nblk(cap), 256, 0, st>>>(means, stride, index, count_dev, cap, 1.0 / cell, sub_bits, keys,
+                                                 vals);
         gsr_status s = count_dev
                            ? gsr_sort_pairs_dev_launch(keys, vals, k2, v2, count_dev, (uint32_t)cap, 32, sort_ws, st)
                            : gsr_sort_pairs_launch(keys, vals, k2, v2, (uint32_t)cap, 32, sort_ws, st);
@@ -393,7 +403,7 @@ extern "C" gsr_status gsr_proximity_launch(const float *map, int64_t n_map, cons
     const double inv_cell = 1.0 / cell;
     const double dd = (double)d_min * (double)d_min;
     gsr_status s = gsr_grid_build_launch(map, n_map, nullptr, nullptr, n_map, cell, w.k, w.v, w.k2, w.v2, w.bucket,
-                                         w.sort, st);
+                                         w.sort, 0, st);
     if (s != GSR_OK) return s;
     k_proximity<<<nblk(n_new), 256, 0, st>>>(map, n_map, nw, n_new, inv_cell, dd, w.k, w.v, w.bucket, keep, w.flag);
     s = gsr_scan_launch(w.flag, n_new, w.off, n_keep, w.scan, st);
