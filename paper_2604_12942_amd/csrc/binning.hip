@@ -16,10 +16,6 @@ __device__ __forceinline__ uint32_t dev_count(const uint32_t *n_dev, uint32_t n_
 }
 
 // ---- generic helpers -------------------------------------------------------------------------
-__global__ void k_copy_u32(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
-}
-
 __global__ void k_fill_u32(uint32_t *__restrict__ dst, uint32_t value, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         dst[i] = value;
@@ -61,9 +57,12 @@ __global__ __launch_bounds__(1024) void k_scan_small(uint32_t *__restrict__ v, i
 // ---- ordered compaction of visible pairs ---------------------------------------------------------
 // Block b covers pairs [b*4096, (b+1)*4096) in round-major order: pair b*4096 + r*256 + t is read by
 // thread t in round r, so every load is coalesced; (round, wave, lane) order is pair order.
+// Also clears the tile ranges (VT2 words), which k_tile_ranges writes for tiles with instances only.
 __global__ __launch_bounds__(256) void k_vis_count(const uint32_t *__restrict__ ntiles, uint32_t VN,
-                                                   uint32_t *__restrict__ bsum) {
+                                                   uint32_t *__restrict__ bsum, uint32_t *__restrict__ ranges,
+                                                   uint32_t VT2) {
     __shared__ uint32_t s_w[4];
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < VT2; i += gridDim.x * 256) ranges[i] = 0u;
     const uint32_t base = blockIdx.x * kSortTile;
     uint32_t c = 0;
 #pragma unroll
@@ -76,10 +75,24 @@ __global__ __launch_bounds__(256) void k_vis_count(const uint32_t *__restrict__ 
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
+// Sum of v[0 .. n) over a 256-thread block (four words of LDS).
+__device__ __forceinline__ uint32_t block_sum_of(const uint32_t *__restrict__ v, uint32_t n, uint32_t *s_w) {
+    uint32_t c = 0;
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < n; i += 256) c += v[i];
+    uint32_t tot;
+    block_excl_scan256(c, s_w, &tot);
+    return tot;
+}
+
+// SELF: boff holds the blocks' plain counts; every block adds up those before it (they fit a few loads
+// per thread), which saves the launch that would scan them, and the last one writes the total.
+template <bool SELF>
 __global__ __launch_bounds__(256) void k_vis_compact(const uint32_t *__restrict__ info, uint32_t VN,
                                                      const uint32_t *__restrict__ boff, uint32_t *__restrict__ keys,
-                                                     uint32_t *__restrict__ vals) {
+                                                     uint32_t *__restrict__ vals, uint32_t *__restrict__ n_vis) {
     __shared__ uint32_t s_cnt[kSortItems * 4];
+    __shared__ uint32_t s_w[4];
     const uint32_t base = blockIdx.x * kSortTile;
     const int w = threadIdx.x >> 6, lane = __lane_id();
     uint64_t m[kSortItems];
@@ -96,7 +109,13 @@ __global__ __launch_bounds__(256) void k_vis_compact(const uint32_t *__restrict_
         s_cnt[threadIdx.x] = wave_incl_scan(c) - c;
     }
     __syncthreads();
-    const uint32_t b0 = boff[blockIdx.x];
+    uint32_t b0;
+    if (SELF) {
+        b0 = block_sum_of(boff, blockIdx.x, s_w);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *n_vis = b0 + boff[blockIdx.x];
+    } else {
+        b0 = boff[blockIdx.x];
+    }
     const uint64_t lt = lanemask_lt();
 #pragma unroll
     for (int r = 0; r < kSortItems; r++) {
@@ -141,39 +160,53 @@ __global__ __launch_bounds__(256) void k_scan_write(const uint32_t *__restrict__
 }
 
 // ---- stable LSD radix sort, 8-bit digits -----------------------------------------------------
-// Block b sorts items [b*kRadixTile, (b+1)*kRadixTile); the histogram counts each block's digits,
-// and the scatter ranks them stably (input order) inside the block.
-constexpr int kRadixItems = 12;
-constexpr int kRadixTile = kSortThreads * kRadixItems;
+// Block b sorts items [b*tile, (b+1)*tile), tile = 256 * ITEMS; the histogram counts each block's
+// digits, and the scatter ranks them stably (input order) inside the block.
+//
+// Long sorts take 12 keys per thread: a block's run of one digit is then 12 keys long on average, so
+// the scattered writes stay wide.  Short ones are bound by one block's latency (dependent loads, then
+// a chain of ITEMS rank rounds) on a chip they do not fill, and take 4: at 100k live keys the scatter
+// went from 13.1 to 5.4 us, at 600k with a second payload from 12.5 to 8, at 1.5M from 14.4 to 10.4 (the
+// histogram then from 5.0 to 6.3).  The line lies where 4 keys per thread have filled the chip sixteen
+// times over (kShortSort); 11M live keys take 12 (7 passes: 0.29 ms against 0.36 before).
+constexpr int kRadixItems = 12, kShortItems = 4;
+constexpr int64_t kShortSort = 1 << 22;  // live items are not known on the host: this is a capacity
+constexpr int kSelfScanBlocks = 64;      // up to here the scatter adds up the histogram rows by itself
+inline int radix_items(int64_t cap) { return cap <= kShortSort ? kShortItems : kRadixItems; }
+inline int64_t radix_blocks(int64_t cap) { return ceil_div(cap > 0 ? cap : 1, kSortThreads * radix_items(cap)); }
+// row stride of the histogram: whole 16-byte words
+inline int64_t radix_stride(int64_t cap) { return ceil_div(radix_blocks(cap), 4) * 4; }
+
+template <int ITEMS>
 __global__ __launch_bounds__(256) void k_radix_hist(const uint32_t *__restrict__ keys, const uint32_t *n_dev,
-                                                    uint32_t n_host, uint32_t cap, int shift, int nblocks,
+                                                    uint32_t n_host, uint32_t cap, int shift, int stride,
                                                     uint32_t *__restrict__ hist) {
-    // Counts are order-free: each thread takes kRadixItems consecutive keys (three 16-byte loads)
-    // and adds a run of equal digits to the block's LDS count in one atomic, so nearly sorted
-    // input (long runs) costs one add per run and shuffled input one per key.
+    // Counts are order-free: each thread takes ITEMS consecutive keys (16-byte loads) and adds a run
+    // of equal digits to the block's LDS count in one atomic, so nearly sorted input (long runs)
+    // costs one add per run and shuffled input one per key.
     __shared__ uint32_t cnt[kRadix];
     const uint32_t n = dev_count(n_dev, n_host, cap);
     // blocks past the live count write nothing: the row scan and the scatter skip them
-    if (blockIdx.x * (uint32_t)kRadixTile >= n) return;
+    if (blockIdx.x * (uint32_t)(kSortThreads * ITEMS) >= n) return;
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const uint32_t first = blockIdx.x * kRadixTile + threadIdx.x * kRadixItems;
+    const uint32_t first = blockIdx.x * (kSortThreads * ITEMS) + threadIdx.x * ITEMS;
     if (first < n) {
-        uint32_t k[kRadixItems];
-        if (first + kRadixItems <= cap && (reinterpret_cast<uintptr_t>(keys) & 15u) == 0) {
+        uint32_t k[ITEMS];
+        if (first + ITEMS <= cap && (reinterpret_cast<uintptr_t>(keys) & 15u) == 0) {
 #pragma unroll
-            for (int q = 0; q < kRadixItems / 4; q++) {
+            for (int q = 0; q < ITEMS / 4; q++) {
                 const uint4 x = *reinterpret_cast<const uint4 *>(keys + first + 4 * q);
                 k[4 * q] = x.x, k[4 * q + 1] = x.y, k[4 * q + 2] = x.z, k[4 * q + 3] = x.w;
             }
         } else {
 #pragma unroll
-            for (int r = 0; r < kRadixItems; r++) k[r] = first + r < cap ? keys[first + r] : 0u;
+            for (int r = 0; r < ITEMS; r++) k[r] = first + r < cap ? keys[first + r] : 0u;
         }
-        const uint32_t m = n - first < (uint32_t)kRadixItems ? n - first : (uint32_t)kRadixItems;
+        const uint32_t m = n - first < (uint32_t)ITEMS ? n - first : (uint32_t)ITEMS;
         uint32_t d = (k[0] >> shift) & (kRadix - 1), run = 1;
 #pragma unroll
-        for (int r = 1; r < kRadixItems; r++) {
+        for (int r = 1; r < ITEMS; r++) {
             if ((uint32_t)r >= m) break;
             const uint32_t dr = (k[r] >> shift) & (kRadix - 1);
             if (dr != d) {
@@ -186,21 +219,21 @@ __global__ __launch_bounds__(256) void k_radix_hist(const uint32_t *__restrict__
         atomicAdd(&cnt[d], run);
     }
     __syncthreads();
-    hist[threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];
+    hist[threadIdx.x * stride + blockIdx.x] = cnt[threadIdx.x];
 }
 
 // Row d of hist (one row per digit, row stride nblocks) is scanned exclusively in place over the
 // blocks that hold live items; the row total goes to totals[d].
-__global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ hist, int nblocks,
-                                                         uint32_t *__restrict__ totals, const uint32_t *n_dev,
-                                                         uint32_t n_host, uint32_t cap) {
+__global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ hist, int nblocks, int stride,
+                                                         int tile, uint32_t *__restrict__ totals,
+                                                         const uint32_t *n_dev, uint32_t n_host, uint32_t cap) {
     // one digit's row per workgroup; each thread owns a contiguous run of the row: sum it, one
     // workgroup scan of the run sums, then rewrite the run as exclusive prefixes.  Runs of up to
     // 16 entries (up to 4096 live blocks) stay in registers, loaded all at once.
     __shared__ uint32_t s_w[4];
-    uint32_t *row = hist + (int64_t)blockIdx.x * nblocks;
+    uint32_t *row = hist + (int64_t)blockIdx.x * stride;
     const uint32_t n = dev_count(n_dev, n_host, cap);
-    const int live = (int)((n + kRadixTile - 1) / kRadixTile);
+    const int live = (int)((n + tile - 1) / tile);
     const int nb = live < nblocks ? live : nblocks;
     const int per = (nb + 255) / 256;
     const int b0 = threadIdx.x * per;
@@ -235,42 +268,64 @@ __global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ 
     if (threadIdx.x == 0) totals[blockIdx.x] = tot;
 }
 
-// Block b sorts items [b*kRadixTile, (b+1)*kRadixTile): wave w owns the quarter from
-// b*kRadixTile + w*kRadixTile/4 on, 64 per round, so (wave, round, lane) order is input order and each wave ranks its items with
-// its own running digit counts, without a workgroup barrier per round; the four waves' counts
-// then give every digit's local start and each wave's offset inside it.
+// Block b sorts its tile: wave w owns a quarter of it, 64 items per round, so (wave, round, lane)
+// order is input order and each wave ranks its items with its own running digit counts, without a
+// workgroup barrier per round; the four waves' counts then give every digit's local start and each
+// wave's offset inside it.  SELF: the histogram rows hold plain counts (at most kSelfScanBlocks of
+// them) and every block adds up the blocks before it and all of them, so that a short sort needs no
+// row scan launch; otherwise the rows are scanned and totals given.
+template <int ITEMS, bool SELF>
 __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                                                        uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
                                                        const uint32_t *__restrict__ vin2, uint32_t *__restrict__ vout2,
                                                        const uint32_t *n_dev, uint32_t n_host, uint32_t cap, int shift,
-                                                       int nblocks, const uint32_t *__restrict__ hist,
+                                                       int stride, const uint32_t *__restrict__ hist,
                                                        const uint32_t *__restrict__ totals) {
-    constexpr int kWaveItems = kRadixTile / 4;
-    __shared__ uint32_t s_keys[kRadixTile];
-    __shared__ uint32_t s_vals[kRadixTile];
+    constexpr int kTile = kSortThreads * ITEMS, kWaveItems = kTile / 4;
+    __shared__ uint32_t s_keys[kTile];
+    __shared__ uint32_t s_vals[kTile];
     __shared__ uint32_t s_wcnt[4][kRadix];  // per-wave running counts, then per-wave starts
-    __shared__ uint32_t s_lstart[kRadix];
-    __shared__ uint32_t s_gbase[kRadix];
+    __shared__ uint32_t s_gbase[kRadix];    // global minus local start of the digit
     __shared__ uint32_t s_w[4];
     const uint32_t n = dev_count(n_dev, n_host, cap);
-    const uint32_t base = blockIdx.x * kRadixTile;
+    const uint32_t base = blockIdx.x * kTile;
     if (base >= n) return;
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-    // global start of digit t for this block
-    const uint32_t dtot = totals[t];
-    const uint32_t dstart = block_excl_scan256(dtot, s_w, nullptr);
-    s_gbase[t] = dstart + hist[t * nblocks + blockIdx.x];
-    for (int k = 0; k < 4; k++) s_wcnt[k][t] = 0;
-    __syncthreads();
-    uint32_t mk[kRadixItems], mv[kRadixItems], mrank[kRadixItems], mv2[kRadixItems];
-    const uint64_t lt = lanemask_lt();
+    // all loads first: the items, and digit t's counts
+    uint32_t mk[ITEMS], mv[ITEMS], mv2[ITEMS], mrank[ITEMS];
     const uint32_t wbase = base + w * kWaveItems;
-    for (int r = 0; r < kRadixItems; r++) {
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
         const uint32_t idx = wbase + r * 64 + lane;
         const bool valid = idx < n;
         mk[r] = valid ? kin[idx] : 0u;
         mv[r] = valid ? vin[idx] : 0u;
         mv2[r] = vin2 ? (valid ? vin2[idx] : 0u) : idx;
+    }
+    uint32_t dtot = 0, before_blocks = 0;
+    if (SELF) {
+        const uint32_t live = (n + kTile - 1) / kTile;
+        const uint4 *row = reinterpret_cast<const uint4 *>(hist + t * stride);
+        for (uint32_t q = 0; 4 * q < live; q++) {
+            const uint4 x = row[q];
+            const uint32_t c[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) {
+                const uint32_t v = 4 * q + i < live ? c[i] : 0u;
+                dtot += v;
+                before_blocks += 4 * q + i < blockIdx.x ? v : 0u;
+            }
+        }
+    } else {
+        dtot = totals[t];
+        before_blocks = hist[t * stride + blockIdx.x];
+    }
+    for (int k = 0; k < 4; k++) s_wcnt[k][t] = 0;
+    __syncthreads();
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
+        const bool valid = wbase + r * 64 + lane < n;
         const uint32_t d = (mk[r] >> shift) & (kRadix - 1);
         const uint64_t peers = match_digit8(d, valid);
         const uint32_t rank = (uint32_t)__popcll(peers & lt);
@@ -279,51 +334,51 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
         mrank[r] = before + rank;
         if (valid && rank == 0) s_wcnt[w][d] = before + (uint32_t)__popcll(peers);
     }
-    __syncthreads();
+    // global start of digit t for this block
+    const uint32_t gstart = block_excl_scan256(dtot, s_w, nullptr) + before_blocks;
     {
         const uint32_t c0 = s_wcnt[0][t], c1 = s_wcnt[1][t], c2 = s_wcnt[2][t], c3 = s_wcnt[3][t];
         const uint32_t ls = block_excl_scan256(c0 + c1 + c2 + c3, s_w, nullptr);
-        s_lstart[t] = ls;
+        s_gbase[t] = gstart - ls;
         s_wcnt[0][t] = ls;
         s_wcnt[1][t] = ls + c0;
         s_wcnt[2][t] = ls + c0 + c1;
         s_wcnt[3][t] = ls + c0 + c1 + c2;
     }
     __syncthreads();
-    for (int r = 0; r < kRadixItems; r++) {
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
         if (wbase + r * 64 + lane < n) {
-            const uint32_t p = s_wcnt[w][(mk[r] >> shift) & (kRadix - 1)] + mrank[r];
-            s_keys[p] = mk[r];
-            s_vals[p] = mv[r];
+            mrank[r] += s_wcnt[w][(mk[r] >> shift) & (kRadix - 1)];
+            s_keys[mrank[r]] = mk[r];
+            s_vals[mrank[r]] = mv[r];
         }
     }
     __syncthreads();
-    const uint32_t bn = (n - base) < (uint32_t)kRadixTile ? (n - base) : (uint32_t)kRadixTile;
-    for (int r = 0; r < kRadixItems; r++) {
+    const uint32_t bn = (n - base) < (uint32_t)kTile ? (n - base) : (uint32_t)kTile;
+    uint32_t dst[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
         const uint32_t p = r * kSortThreads + t;
         if (p < bn) {
             const uint32_t k = s_keys[p];
-            const uint32_t d = (k >> shift) & (kRadix - 1);
-            const uint32_t dst = s_gbase[d] + (p - s_lstart[d]);
-            kout[dst] = k;
-            vout[dst] = s_vals[p];
+            dst[r] = s_gbase[(k >> shift) & (kRadix - 1)] + p;
+            kout[dst[r]] = k;
+            vout[dst[r]] = s_vals[p];
         }
     }
     if (vout2) {
         // the second payload takes the same permutation through the same LDS staging (without
         // vin2 it is each item's input position)
         __syncthreads();
-        for (int r = 0; r < kRadixItems; r++) {
-            if (wbase + r * 64 + lane < n)
-                s_vals[s_wcnt[w][(mk[r] >> shift) & (kRadix - 1)] + mrank[r]] = mv2[r];
-        }
+#pragma unroll
+        for (int r = 0; r < ITEMS; r++)
+            if (wbase + r * 64 + lane < n) s_vals[mrank[r]] = mv2[r];
         __syncthreads();
-        for (int r = 0; r < kRadixItems; r++) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; r++) {
             const uint32_t p = r * kSortThreads + t;
-            if (p < bn) {
-                const uint32_t d = (s_keys[p] >> shift) & (kRadix - 1);
-                vout2[s_gbase[d] + (p - s_lstart[d])] = s_vals[p];
-            }
+            if (p < bn) vout2[dst[r]] = s_vals[p];
         }
     }
 }
@@ -351,17 +406,24 @@ __global__ __launch_bounds__(256) void k_inst_count(const uint32_t *__restrict__
 // writes are coalesced.  A pair's tiles are emitted row-major and consecutively ("emission
 // order").  With pair_gid: the emission-ordered list of visible pairs and the emission index of
 // each pair's first instance.  (Each instance's emission index is its position here: the sort's
-// first pass generates it as the second payload.)
+// first pass generates it as the second payload.)  SELF: as in k_vis_compact; the block of the last
+// pairs writes the instance count.
+template <bool SELF>
 __global__ __launch_bounds__(256) void k_inst_emit(const uint32_t *__restrict__ sorted_gid, const uint32_t *n_vis,
                                                    uint32_t cap_vis, const uint32_t *__restrict__ info, uint32_t VN,
                                                    uint32_t n, uint32_t T, uint32_t ntx,
                                                    const uint32_t *__restrict__ boff, uint32_t *__restrict__ ikey,
                                                    uint32_t *__restrict__ ival,
                                                    uint32_t *__restrict__ pair_gid, uint32_t *__restrict__ pair_first,
+                                                   uint32_t *__restrict__ n_pairs, uint32_t *__restrict__ n_inst,
                                                    uint32_t cap) {
     __shared__ uint32_t s_w[4];
     __shared__ uint32_t s_off[256], s_gid[256], s_r0[256], s_r1[256];
     const uint32_t nv = dev_count(n_vis, 0, cap_vis);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (n_pairs) *n_pairs = nv;
+        if (SELF && nv == 0) *n_inst = 0u;
+    }
     if (blockIdx.x * 256 >= nv) return;
     const uint32_t idx = blockIdx.x * 256 + threadIdx.x;
     const bool valid = idx < nv;
@@ -369,7 +431,8 @@ __global__ __launch_bounds__(256) void k_inst_emit(const uint32_t *__restrict__ 
     const uint32_t c = valid ? info[gid] : 0u;
     uint32_t tot;
     const uint32_t excl = block_excl_scan256(c, s_w, &tot);
-    const uint32_t base = boff[blockIdx.x];
+    const uint32_t base = SELF ? block_sum_of(boff, blockIdx.x, s_w) : boff[blockIdx.x];
+    if (SELF && (blockIdx.x + 1) * 256 >= nv && threadIdx.x == 0) *n_inst = base + tot;
     s_off[threadIdx.x] = excl;
     s_gid[threadIdx.x] = gid;
     s_r0[threadIdx.x] = valid ? info[2 * VN + gid] : 0u;
@@ -421,28 +484,185 @@ __global__ void k_tile_keys(const uint32_t *__restrict__ ranges, uint32_t VT, ui
     }
 }
 
-__global__ void k_tile_ranges(const uint32_t *__restrict__ keys, const uint32_t *n_inst, uint32_t cap,
-                              uint32_t *__restrict__ ranges) {
-    const uint32_t m = dev_count(n_inst, 0, cap);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
+// [start, end) of every view-tile with instances (ranges were cleared before).  An instance count
+// above the capacity leaves incomplete lists.  Rather than render them, the frame is emptied: no
+// pair visible (tile_info row 0 cleared), every tile range empty and no emitted pair, so the render,
+// backward, pair sums, projection backward, fused Adam and visible list that follow on the stream do
+// nothing.
+__global__ void k_tile_ranges(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ n_inst, uint32_t cap,
+                              uint32_t *__restrict__ ranges, uint32_t *__restrict__ ntiles, uint32_t VN,
+                              uint32_t *__restrict__ n_pairs) {
+    const uint32_t m = *n_inst, stride = gridDim.x * blockDim.x;
+    if (m > cap) {
+        for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < VN; i += stride) ntiles[i] = 0u;
+        if (n_pairs && blockIdx.x == 0 && threadIdx.x == 0) *n_pairs = 0u;
+        return;
+    }
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
         const uint32_t k = keys[i];
         if (i == 0 || keys[i - 1] != k) ranges[2 * k] = i;
         if (i + 1 == m || keys[i + 1] != k) ranges[2 * k + 1] = i + 1;
     }
 }
 
-// An instance count above the capacity leaves incomplete lists.  Rather than render them, the
-// frame is emptied: no pair visible (tile_info row 0 cleared), every tile range empty and no
-// emitted pair, so the render, backward, pair sums, projection backward, fused Adam and visible
-// list that follow on the stream do nothing.  A no-op when the instances fit.
-__global__ void k_overflow_clear(const uint32_t *__restrict__ n_inst, uint32_t cap, uint32_t *__restrict__ ntiles,
-                                 uint32_t VN, uint32_t *__restrict__ ranges, uint32_t VT2,
-                                 uint32_t *__restrict__ n_pairs) {
-    if (*n_inst <= cap) return;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < VN; i += stride) ntiles[i] = 0u;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < VT2; i += stride) ranges[i] = 0u;
-    if (n_pairs && blockIdx.x == 0 && threadIdx.x == 0) *n_pairs = 0u;
+// ---- small problems: one workgroup -------------------------------------------------------------
+// Up to kSmallSort items fit one 1024-thread block's LDS.  A launch of the general path costs 2 to 5
+// us on an idle chip whatever its work, so the 17 launches from the visible pairs to the emission
+// offsets (compaction, four radix passes, instance scan) become one, and the tile order's four one.
+constexpr int kSmallThreads = 1024, kSmallRounds = 8, kSmallSort = kSmallThreads * kSmallRounds;
+
+// Exclusive prefix of one value per thread over the 1024-thread block; *total its sum.
+__device__ __forceinline__ uint32_t block_excl_scan1024(uint32_t v, uint32_t *s_w, uint32_t *total) {
+    const int w = threadIdx.x >> 6;
+    const uint32_t inc = wave_incl_scan(v);
+    if (__lane_id() == 63) s_w[w] = inc;
+    __syncthreads();
+    uint32_t base = 0, tot = 0;
+#pragma unroll
+    for (int k = 0; k < 16; k++) {
+        base += k < w ? s_w[k] : 0u;
+        tot += s_w[k];
+    }
+    __syncthreads();
+    *total = tot;
+    return base + inc - v;
+}
+
+// Stable positions of n items by their 8-bit digits.  Thread t of wave w holds items w * rounds * 64 +
+// r * 64 + lane, r < rounds = ceil(n / 1024), so that (wave, round, lane) order is item order.
+__device__ __forceinline__ void small_positions(const uint32_t d[kSmallRounds], uint32_t n, int rounds,
+                                                uint32_t (*s_cnt)[kRadix], uint32_t *s_w,
+                                                uint32_t pos[kSmallRounds]) {
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    for (int q = t; q < 16 * kRadix; q += kSmallThreads) s_cnt[q >> kRadixBits][q & (kRadix - 1)] = 0u;
+    __syncthreads();
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        if (r >= rounds) break;
+        const bool valid = (uint32_t)((w * rounds + r) * 64 + lane) < n;
+        const uint64_t peers = match_digit8(d[r], valid);
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t before = s_cnt[w][d[r]];
+        pos[r] = before + rank;
+        if (valid && rank == 0) s_cnt[w][d[r]] = before + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t c[16], sum = 0, tot;
+    if (t < kRadix) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) sum += c[k] = s_cnt[k][t];
+    }
+    uint32_t run = block_excl_scan1024(sum, s_w, &tot);
+    if (t < kRadix) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            s_cnt[k][t] = run;
+            run += c[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        if (r >= rounds) break;
+        pos[r] += s_cnt[w][d[r]];
+    }
+}
+
+// Visible pairs of VN <= kSmallSort, stably sorted by depth bits: their rows, count, the exclusive
+// instance offset of every 256 of them and the instance count.  Clears the tile ranges.
+__global__ __launch_bounds__(kSmallThreads) void k_bin_small(const uint32_t *__restrict__ info, uint32_t VN,
+                                                             uint32_t *__restrict__ sorted_gid,
+                                                             uint32_t *__restrict__ boff, uint32_t *__restrict__ n_vis,
+                                                             uint32_t *__restrict__ n_inst,
+                                                             uint32_t *__restrict__ ranges, uint32_t VT2) {
+    __shared__ uint32_t s_k[kSmallSort], s_v[kSmallSort];
+    __shared__ uint32_t s_cnt[16][kRadix];
+    __shared__ uint32_t s_w[16];
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    for (uint32_t i = t; i < VT2; i += kSmallThreads) ranges[i] = 0u;
+    // ordered compaction: thread t reads pairs r * 1024 + t
+    uint32_t nt[kSmallRounds], z[kSmallRounds];
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        const uint32_t e = r * kSmallThreads + t;
+        nt[r] = e < VN ? info[e] : 0u;
+        z[r] = e < VN ? info[VN + e] : 0u;  // (unwritten where no tile is, and not used then)
+    }
+    uint32_t n = 0;
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        if ((uint32_t)(r * kSmallThreads) >= VN) break;
+        uint32_t tot;
+        const uint32_t p = n + block_excl_scan1024(nt[r] ? 1u : 0u, s_w, &tot);
+        if (nt[r]) {
+            s_k[p] = z[r];
+            s_v[p] = r * kSmallThreads + t;
+        }
+        n += tot;
+    }
+    __syncthreads();
+    const int rounds = (int)((n + kSmallThreads - 1) / kSmallThreads);
+    const uint32_t first = (uint32_t)(w * rounds * 64 + lane);
+    for (int shift = 0; shift < 32; shift += kRadixBits) {
+        uint32_t k[kSmallRounds], v[kSmallRounds], d[kSmallRounds], pos[kSmallRounds];
+#pragma unroll
+        for (int r = 0; r < kSmallRounds; r++) {
+            if (r >= rounds) break;
+            const uint32_t i = first + r * 64;
+            k[r] = i < n ? s_k[i] : 0u;
+            v[r] = i < n ? s_v[i] : 0u;
+            d[r] = (k[r] >> shift) & (kRadix - 1);
+        }
+        small_positions(d, n, rounds, s_cnt, s_w, pos);  // (barriers inside: every item has been read)
+#pragma unroll
+        for (int r = 0; r < kSmallRounds; r++) {
+            if (r >= rounds) break;
+            if (first + r * 64 < n) {
+                s_k[pos[r]] = k[r];
+                s_v[pos[r]] = v[r];
+            }
+        }
+        __syncthreads();
+    }
+    uint32_t run = 0;
+    for (int r = 0; r < rounds; r++) {
+        const uint32_t i = r * kSmallThreads + t;
+        const uint32_t g = i < n ? s_v[i] : 0u, c = i < n ? info[g] : 0u;
+        uint32_t tot;
+        const uint32_t p = run + block_excl_scan1024(c, s_w, &tot);
+        if (i < n) {
+            sorted_gid[i] = g;
+            if ((i & 255u) == 0) boff[i >> 8] = p;
+        }
+        run += tot;
+    }
+    if (t == 0) {
+        *n_vis = n;
+        *n_inst = run;
+    }
+}
+
+// Longest-first order of VT <= kSmallSort view-tiles.
+__global__ __launch_bounds__(kSmallThreads) void k_tile_order_small(const uint32_t *__restrict__ ranges, uint32_t VT,
+                                                                    uint32_t *__restrict__ order) {
+    __shared__ uint32_t s_cnt[16][kRadix];
+    __shared__ uint32_t s_w[16];
+    const int rounds = (int)((VT + kSmallThreads - 1) / kSmallThreads);
+    const uint32_t first = (uint32_t)((threadIdx.x >> 6) * rounds * 64 + (threadIdx.x & 63));
+    uint32_t d[kSmallRounds], pos[kSmallRounds];
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        if (r >= rounds) break;
+        const uint32_t i = first + r * 64;
+        d[r] = i < VT ? lpt_key(ranges[2 * i + 1] - ranges[2 * i]) : 0u;
+    }
+    small_positions(d, VT, rounds, s_cnt, s_w, pos);
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; r++) {
+        if (r >= rounds) break;
+        if (first + r * 64 < VT) order[pos[r]] = first + r * 64;
+    }
 }
 
 }  // namespace gsr
@@ -468,9 +688,9 @@ BinWs layout(void *base, int64_t VN, int64_t cap, int64_t VT) {
     BinWs w{};
     const int64_t nb_vn = ceil_div(VN > 0 ? VN : 1, kSortTile);
     // histogram rows are as long as the largest sort's block count
-    int64_t nbm = ceil_div(VN > 0 ? VN : 1, kRadixTile), nbc = ceil_div(cap > 0 ? cap : 1, kRadixTile);
+    int64_t nbm = radix_stride(VN), nbc = radix_stride(cap);
     nbm = nbm > nbc ? nbm : nbc;
-    nbc = ceil_div(VT > 0 ? VT : 1, kRadixTile);
+    nbc = radix_stride(VT);
     nbm = nbm > nbc ? nbm : nbc;
     char *p = static_cast<char *>(base);
     size_t off = 0;
@@ -488,18 +708,35 @@ BinWs layout(void *base, int64_t VN, int64_t cap, int64_t VT) {
     return w;
 }
 
+template <int ITEMS>
+void radix_pass(const uint32_t *k, const uint32_t *v, uint32_t *k2, uint32_t *v2, const uint32_t *win, uint32_t *wout,
+                const uint32_t *n_dev, uint32_t n_host, uint32_t cap, int shift, uint32_t *hist, uint32_t *totals,
+                hipStream_t st) {
+    const int nb = (int)radix_blocks(cap), stride = (int)radix_stride(cap);
+    k_radix_hist<ITEMS><<<nb, kSortThreads, 0, st>>>(k, n_dev, n_host, cap, shift, stride, hist);
+    if constexpr (ITEMS == kShortItems) {
+        if (nb <= kSelfScanBlocks) {
+            k_radix_scatter<ITEMS, true><<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, wout, n_dev, n_host, cap,
+                                                                      shift, stride, hist, totals);
+            return;
+        }
+    }
+    k_radix_scan_rows<<<kRadix, 256, 0, st>>>(hist, nb, stride, kSortThreads * ITEMS, totals, n_dev, n_host, cap);
+    k_radix_scatter<ITEMS, false><<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, wout, n_dev, n_host, cap, shift,
+                                                               stride, hist, totals);
+}
+
 gsr_status radix_sort(uint32_t *&k, uint32_t *&v, uint32_t *&k2, uint32_t *&v2, const uint32_t *n_dev,
                       uint32_t n_host, uint32_t cap, int bits, uint32_t *hist, uint32_t *totals, hipStream_t st,
                       uint32_t **w = nullptr, uint32_t **w2 = nullptr, bool w_is_position = false) {
-    const int nb = (int)ceil_div(cap, kRadixTile);
     for (int shift = 0; shift < bits; shift += kRadixBits) {
-        k_radix_hist<<<nb, kSortThreads, 0, st>>>(k, n_dev, n_host, cap, shift, nb, hist);
-        k_radix_scan_rows<<<kRadix, 256, 0, st>>>(hist, nb, totals, n_dev, n_host, cap);
         // w_is_position: the second payload starts as each item's input position, generated by
         // the first pass instead of read
         const uint32_t *win = w && !(w_is_position && shift == 0) ? *w : nullptr;
-        k_radix_scatter<<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev,
-                                                     n_host, cap, shift, nb, hist, totals);
+        if (radix_items(cap) == kShortItems)
+            radix_pass<kShortItems>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist, totals, st);
+        else
+            radix_pass<kRadixItems>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist, totals, st);
         uint32_t *tk = k, *tv = v;
         k = k2; v = v2; k2 = tk; v2 = tv;
         if (w) {
@@ -529,19 +766,33 @@ extern "C" gsr_status gsr_bin_sort_launch(uint32_t *info, int64_t n, int V, int 
     const uint32_t T = (uint32_t)(ntx * nty);
     const int64_t VT = (int64_t)V * T;
     BinWs w = layout(ws, VN, cap, VT);
-    const int nb_vn = (int)ceil_div(VN > 0 ? VN : 1, kSortTile);
-    // 1. ordered compaction of visible pairs: keys = depth bits, values = v*n + i
-    k_vis_count<<<nb_vn, 256, 0, st>>>(info, (uint32_t)VN, w.vis_b);
-    k_scan_small<<<1, 1024, 0, st>>>(w.vis_b, nb_vn, w.n_vis);
-    k_vis_compact<<<nb_vn, 256, 0, st>>>(info, (uint32_t)VN, w.vis_b, w.zk0, w.zv0);
-    // 2. stable sort by depth bits (32 bits, 4 passes: result back in zk0 / zv0)
+    const int nb_vn = (int)ceil_div(VN > 0 ? VN : 1, kSortTile), nb_p = (int)ceil_div(VN > 0 ? VN : 1, 256);
+    const uint32_t capv = (uint32_t)(VN > 0 ? VN : 1);
+    // block counts few enough for every block to add up those before it (at most eight 4-byte loads per
+    // thread); beyond, the quadratic work would outgrow the launch it saves
+    const bool self = nb_p <= 2048;
+    const bool small = VN <= kSmallSort && 2 * VT <= 4 * kSmallSort;
     uint32_t *k = w.zk0, *v = w.zv0, *k2 = w.zk1, *v2 = w.zv1;
-    gsr_status s = radix_sort(k, v, k2, v2, w.n_vis, 0, (uint32_t)(VN > 0 ? VN : 1), 32, w.hist, w.totals, st);
-    if (s != GSR_OK) return s;
-    // 3. instance counts in depth order, scan, emission
-    const int nb_p = (int)ceil_div(VN > 0 ? VN : 1, 256);
-    k_inst_count<<<nb_p < 4096 ? nb_p : 4096, 256, 0, st>>>(v, w.n_vis, (uint32_t)(VN > 0 ? VN : 1), info, w.cnt_b);
-    k_scan_small<<<1, 1024, 0, st>>>(w.cnt_b, nb_p, n_inst, w.n_vis, 256u);
+    gsr_status s;
+    if (small) {
+        k_bin_small<<<1, kSmallThreads, 0, st>>>(info, (uint32_t)VN, v, w.cnt_b, w.n_vis, n_inst, ranges,
+                                                 (uint32_t)(2 * VT));
+    } else {
+        // 1. ordered compaction of visible pairs: keys = depth bits, values = v*n + i
+        k_vis_count<<<nb_vn, 256, 0, st>>>(info, (uint32_t)VN, w.vis_b, ranges, (uint32_t)(2 * VT));
+        if (self) {
+            k_vis_compact<true><<<nb_vn, 256, 0, st>>>(info, (uint32_t)VN, w.vis_b, w.zk0, w.zv0, w.n_vis);
+        } else {
+            k_scan_small<<<1, 1024, 0, st>>>(w.vis_b, nb_vn, w.n_vis);
+            k_vis_compact<false><<<nb_vn, 256, 0, st>>>(info, (uint32_t)VN, w.vis_b, w.zk0, w.zv0, w.n_vis);
+        }
+        // 2. stable sort by depth bits (32 bits, 4 passes: result back in zk0 / zv0)
+        s = radix_sort(k, v, k2, v2, w.n_vis, 0, capv, 32, w.hist, w.totals, st);
+        if (s != GSR_OK) return s;
+        // 3. instance counts in depth order, scan, emission
+        k_inst_count<<<nb_p < 4096 ? nb_p : 4096, 256, 0, st>>>(v, w.n_vis, capv, info, w.cnt_b);
+        if (!self) k_scan_small<<<1, 1024, 0, st>>>(w.cnt_b, nb_p, n_inst, w.n_vis, 256u);
+    }
     // the instance sort runs ceil(bits/8) passes; emit into the buffer that makes the last
     // pass land in the sorted-values output (inst_emit when asked for, else inst_gid)
     const int tbits = bit_length((uint64_t)V * T - 1) > 0 ? bit_length((uint64_t)V * T - 1) : 1;
@@ -551,24 +802,23 @@ extern "C" gsr_status gsr_bin_sort_launch(uint32_t *info, int64_t n, int V, int 
     uint32_t *inst_emit = em ? em->inst_emit : nullptr;
     uint32_t *ew = inst_emit ? ((passes % 2 == 0) ? inst_emit : w.iw1) : nullptr;
     uint32_t *ow = inst_emit ? ((passes % 2 == 0) ? w.iw1 : inst_emit) : nullptr;
-    k_inst_emit<<<nb_p, 256, 0, st>>>(v, w.n_vis, (uint32_t)(VN > 0 ? VN : 1), info, (uint32_t)VN, (uint32_t)n, T,
-                                      (uint32_t)ntx, w.cnt_b, ek, ev, em ? em->pair_gid : nullptr,
-                                      em ? em->pair_first : nullptr, (uint32_t)cap);
-    if (em) k_copy_u32<<<1, 64, 0, st>>>(w.n_vis, em->n_pairs, 1);
+    // (the small path has scanned the offsets)
+    const auto emit = self && !small ? k_inst_emit<true> : k_inst_emit<false>;
+    emit<<<nb_p, 256, 0, st>>>(v, w.n_vis, capv, info, (uint32_t)VN, (uint32_t)n, T, (uint32_t)ntx, w.cnt_b, ek, ev,
+                               em ? em->pair_gid : nullptr, em ? em->pair_first : nullptr, em ? em->n_pairs : nullptr,
+                               n_inst, (uint32_t)cap);
     // 4. stable sort by view-tile (carrying the emission index along when asked for)
     s = radix_sort(ek, ev, ok, ov, n_inst, 0, (uint32_t)cap, passes * kRadixBits, w.hist, w.totals, st,
                    inst_emit ? &ew : nullptr, inst_emit ? &ow : nullptr, true);
     if (s != GSR_OK) return s;
-    // 5. per view-tile [start, end)
-    k_fill_u32<<<(int)ceil_div(2 * (int64_t)V * T, 256) < 4096 ? (int)ceil_div(2 * (int64_t)V * T, 256) : 4096, 256, 0,
-                 st>>>(ranges, 0u, 2 * (int64_t)V * T);
+    // 5. per view-tile [start, end), or an empty frame when the instances do not fit
     const int nr = (int)(ceil_div(cap, 256) < 8192 ? ceil_div(cap, 256) : 8192);
-    k_tile_ranges<<<nr, 256, 0, st>>>(ek, n_inst, (uint32_t)cap, ranges);
-    k_overflow_clear<<<256, 256, 0, st>>>(n_inst, (uint32_t)cap, info, (uint32_t)VN, ranges, (uint32_t)(2 * VT),
-                                          em ? em->n_pairs : nullptr);
+    k_tile_ranges<<<nr, 256, 0, st>>>(ek, n_inst, (uint32_t)cap, ranges, info, (uint32_t)VN, em ? em->n_pairs : nullptr);
     // 6. longest-processing-time order of the view-tiles (descending instance count, to 1/16 of
     // an octave): one 8-bit pass, whose values land in tile_order
-    if (tile_order) {
+    if (tile_order && VT <= kSmallSort) {
+        k_tile_order_small<<<1, kSmallThreads, 0, st>>>(ranges, (uint32_t)VT, tile_order);
+    } else if (tile_order) {
         const int nt = (int)(ceil_div(VT, 256) < 4096 ? ceil_div(VT, 256) : 4096);
         k_tile_keys<<<nt, 256, 0, st>>>(ranges, (uint32_t)VT, w.tk0, w.tv1);
         uint32_t *a = w.tk0, *b = w.tv1, *c = w.tk1, *d = tile_order;
@@ -615,7 +865,7 @@ extern "C" gsr_status gsr_scan_launch(const uint32_t *in, int64_t n, uint32_t *o
 // ping-ponging between (k, v) and (k2, v2): the result is in (k, v) when ceil(bits / 8) is even,
 // else in (k2, v2).  ws: gsr_sort_pairs_ws_bytes(n).
 extern "C" size_t gsr_sort_pairs_ws_bytes(int64_t n) {
-    return (size_t)((int64_t)kRadix * ceil_div(n > 0 ? n : 1, kRadixTile) * 4 + kRadix * 4 + 512);
+    return (size_t)((int64_t)kRadix * radix_stride(n) * 4 + kRadix * 4 + 512);
 }
 
 // As gsr_sort_pairs_launch with the count read on the device (*n_dev, at most cap).
@@ -624,7 +874,7 @@ extern "C" gsr_status gsr_sort_pairs_dev_launch(uint32_t *k, uint32_t *v, uint32
                                                 hipStream_t st) {
     if (cap == 0) return GSR_OK;
     uint32_t *hist = static_cast<uint32_t *>(ws);
-    uint32_t *totals = hist + (size_t)kRadix * ceil_div(cap, kRadixTile);
+    uint32_t *totals = hist + (size_t)kRadix * radix_stride(cap);
     return radix_sort(k, v, k2, v2, n_dev, cap, cap, bits, hist, totals, st);
 }
 
@@ -632,7 +882,7 @@ extern "C" gsr_status gsr_sort_pairs_launch(uint32_t *k, uint32_t *v, uint32_t *
                                             void *ws, hipStream_t st) {
     if (n == 0) return GSR_OK;
     uint32_t *hist = static_cast<uint32_t *>(ws);
-    uint32_t *totals = hist + (size_t)kRadix * ceil_div(n, kRadixTile);
+    uint32_t *totals = hist + (size_t)kRadix * radix_stride(n);
     return radix_sort(k, v, k2, v2, nullptr, n, n, bits, hist, totals, st);
 }
 
