@@ -886,3 +886,19 @@ extern "C" gsr_status gsr_sort_pairs_launch(uint32_t *k, uint32_t *v, uint32_t *
     return radix_sort(k, v, k2, v2, nullptr, n, n, bits, hist, totals, st);
 }
 
+
+// Stable LSD radix sort of n keys by their low `bits`, carrying a payload v and the items' input
+// positions w: k[0], v[0] in, k[1], v[1], w[0], w[1] buffers; on return [0] of each is the result.
+extern "C" gsr_status gsr_sort_positions_launch(uint32_t *k[2], uint32_t *v[2], uint32_t *w[2], uint32_t n, int bits,
+                                                void *ws, hipStream_t st) {
+    if (n == 0) return GSR_OK;
+    uint32_t *hist = static_cast<uint32_t *>(ws);
+    uint32_t *totals = hist + (size_t)kRadix * radix_stride(n);
+    return radix_sort(k[0], v[0], k[1], v[1], nullptr, n, n, bits, hist, totals, st, &w[0], &w[1], true);
+}
+
+// v[0 .. nb) replaced by its exclusive prefix sums, *total their sum (one block).
+extern "C" gsr_status gsr_exclusive_scan_small_launch(uint32_t *v, int nb, uint32_t *total, hipStream_t st) {
+    k_scan_small<<<1, 1024, 0, st>>>(v, nb, total);
+    return last_launch();
+}

@@ -2,10 +2,10 @@
 // Gaussian initialisation (Sec. III-B, Eq. 3, 5, 6).
 //
 // Voxel PCA: every point gets a packed 32-bit voxel key and a 64-bit SplitMix64 hash of
-// (seed XOR index); three stable 32-bit radix sorts (hash low word, hash high word, key) group
-// the points by voxel in ascending key order and, inside a voxel, by ascending hash.  A scan of
-// the voxel heads numbers the voxels; one thread per voxel then fits its first (at most 32)
-// points in double precision: mean, biased covariance, cyclic Jacobi eigensystem, canonical
+// (seed XOR index); two stable radix sorts (the hash's leading bits, then the key) group the points
+// by voxel in ascending key order and, inside a voxel, by those bits; the few points of one voxel
+// that share them are put in order of the whole hash when the voxels are numbered.  One thread per
+// voxel then fits its first (at most 32) points in double precision: mean, biased covariance, cyclic Jacobi eigensystem, canonical
 // frame, planar / linear / unreliable class, and the trace of the descriptor's direction
 // covariance, which Eq. 1-2 with isotropic point covariance sigma^2 I reduce to
 // sigma^2 / N * sum_{m != k} (l_m + l_k) / (l_k - l_m)^2.  Given per-point world covariances,
@@ -30,9 +30,9 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
 
 // packed key: (kx + 1024) << 21 | (ky + 1024) << 10 | (kz + 511); kx, ky in [-1024, 1023],
 // kz in [-511, 511] (so the all-ones word never names a voxel and marks points outside)
-__global__ void k_vox_prep(const float *__restrict__ pts, int64_t n, uint64_t seed, uint32_t *__restrict__ key,
-                           uint32_t *__restrict__ hlo, uint32_t *__restrict__ hhi, uint32_t *__restrict__ idx) {
-    // hlo doubles as the first sort's key array
+__global__ void k_vox_prep(const float *__restrict__ pts, int64_t n, uint64_t seed, int hash_bits,
+                           uint32_t *__restrict__ key, uint32_t *__restrict__ hash, uint32_t *__restrict__ n_outside) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_outside = 0u;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const float x = pts[i], y = pts[n + i], z = pts[2 * n + i];
         const float kxf = floorf(x / kVoxel), kyf = floorf(y / kVoxel), kzf = floorf(z / kVoxel);
@@ -41,40 +41,117 @@ __global__ void k_vox_prep(const float *__restrict__ pts, int64_t n, uint64_t se
         key[i] = in ? ((uint32_t)((int)kxf + 1024) << 21) | ((uint32_t)((int)kyf + 1024) << 10) |
                           (uint32_t)((int)kzf + 511)
                     : kOutside;
-        const uint64_t h = splitmix64(seed ^ (uint64_t)i);
-        hlo[i] = (uint32_t)h;
-        hhi[i] = (uint32_t)(h >> 32);
-        idx[i] = (uint32_t)i;
+        hash[i] = (uint32_t)(splitmix64(seed ^ (uint64_t)i) >> (64 - hash_bits));
     }
 }
 
-__global__ void k_gather_u32(const uint32_t *__restrict__ src, const uint32_t *__restrict__ idx, int64_t n,
-                             uint32_t *__restrict__ dst) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = src[idx[i]];
+// Voxel heads per block of 256 ROUNDS sorted points (round-major, coalesced).
+template <int ROUNDS>
+__global__ __launch_bounds__(256) void k_vox_heads(const uint32_t *__restrict__ skey, int64_t n,
+                                                   uint32_t *__restrict__ bsum) {
+    __shared__ uint32_t s_w[4];
+    const int64_t base = (int64_t)blockIdx.x * (256 * ROUNDS);
+    uint32_t c = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        const int64_t e = base + r * kSortThreads + threadIdx.x;
+        if (e < n) {
+            const uint32_t k = skey[e];
+            c += k != kOutside && (e == 0 || k != skey[e - 1]) ? 1u : 0u;
+        }
+    }
+    uint32_t tot;
+    block_excl_scan256(c, s_w, &tot);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-__global__ void k_vox_heads(const uint32_t *__restrict__ skey, int64_t n, uint32_t *__restrict__ head) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        head[i] = (skey[i] != kOutside && (i == 0 || skey[i] != skey[i - 1])) ? 1u : 0u;
-}
-
-__global__ void k_vox_assign(const uint32_t *__restrict__ skey, const uint32_t *__restrict__ sidx,
-                             const uint32_t *__restrict__ head, const uint32_t *__restrict__ hscan, int64_t n,
-                             gsr_voxels V) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t p = sidx[i];
-        V.point_order[i] = p;
-        if (skey[i] == kOutside) {
+// Numbers the voxels, writes the points' order and voxels.  Points of one voxel whose leading hash bits
+// agree form a run that the sort left in index order: its first point writes the run in order of the
+// whole hash (distinct: SplitMix64 is a bijection).  bsum: the blocks' head counts, scanned when
+// `scanned`, else added up here (the last block then writes the voxel count).
+template <int ROUNDS>
+__global__ __launch_bounds__(256) void k_vox_assign(const uint32_t *__restrict__ skey, const uint32_t *__restrict__ sidx,
+                                                    int64_t n, uint64_t seed, int hash_bits,
+                                                    const uint32_t *__restrict__ bsum, bool scanned, gsr_voxels V) {
+    __shared__ uint32_t s_cnt[ROUNDS * 4];
+    __shared__ uint32_t s_w[4];
+    const int64_t base = (int64_t)blockIdx.x * (256 * ROUNDS);
+    const int w = threadIdx.x >> 6, lane = __lane_id();
+    uint32_t b0;
+    if (scanned) {
+        b0 = bsum[blockIdx.x];
+    } else {
+        uint32_t c = 0;
+#pragma unroll 4
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256) c += bsum[i];
+        block_excl_scan256(c, s_w, &b0);
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *V.n_voxels = b0 + bsum[blockIdx.x];
+    }
+    uint64_t m[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        const int64_t e = base + r * 256 + threadIdx.x;
+        const uint32_t k = e < n ? skey[e] : kOutside;
+        m[r] = __ballot(k != kOutside && (e == 0 || k != skey[e - 1]));
+        if (lane == 0) s_cnt[r * 4 + w] = (uint32_t)__popcll(m[r]);
+    }
+    __syncthreads();
+    if (threadIdx.x < ROUNDS * 4) {
+        const uint32_t c = s_cnt[threadIdx.x];
+        s_cnt[threadIdx.x] = wave_incl_scan(c) - c;
+    }
+    __syncthreads();
+    const int sh = 64 - hash_bits;
+#pragma unroll 4
+    for (int r = 0; r < ROUNDS; r++) {
+        const int64_t e = base + r * 256 + threadIdx.x;
+        const bool in = e < n;
+        const uint32_t k = in ? skey[e] : 0u, p = in ? sidx[e] : 0u;
+        const uint64_t out = __ballot(in && k == kOutside);
+        if (out && lane == __builtin_ctzll(out)) atomicAdd(V.n_outside, (uint32_t)__popcll(out));
+        if (!in) continue;
+        const bool head = (m[r] >> lane) & 1ull;
+        if (k == kOutside) {
             V.point_voxel[p] = kOutside;
-            atomicAdd(V.n_outside, 1u);
+        } else {
+            const uint32_t v = b0 + s_cnt[r * 4 + w] + (uint32_t)__popcll(m[r] & lanemask_lt()) + (head ? 1u : 0u) - 1u;
+            V.point_voxel[p] = v;
+            if (head) {
+                V.start[v] = (uint32_t)e;
+                V.key[v] = k;
+            }
+        }
+        const uint64_t h = splitmix64(seed ^ (uint64_t)p) >> sh;
+        auto same = [&](int64_t q) { return skey[q] == k && splitmix64(seed ^ (uint64_t)sidx[q]) >> sh == h; };
+        if (e > 0 && same(e - 1)) continue;  // the run's first point writes it
+        int64_t end = e + 1;
+        while (end < n && same(end)) end++;
+        if (end == e + 1) {
+            V.point_order[e] = p;
             continue;
         }
-        const uint32_t v = hscan[i] + head[i] - 1u;
-        V.point_voxel[p] = v;
-        if (head[i]) {
-            V.start[v] = (uint32_t)i;
-            V.key[v] = skey[i];
+        for (int64_t a = e; a < end; a++) {
+            const uint32_t pa = sidx[a];
+            const uint64_t ha = splitmix64(seed ^ (uint64_t)pa);
+            int64_t rank = 0;
+            for (int64_t q = e; q < end; q++) rank += splitmix64(seed ^ (uint64_t)sidx[q]) < ha ? 1 : 0;
+            V.point_order[e + rank] = pa;
+        }
+    }
+}
+
+// The points as records, so that a fit gathers one cache line per point and not one per component:
+// (x, y, z, 0), or with covariances (x, y, z, xx, xy, xz, yy, yz); zz stays where it is.
+template <bool COV>
+__global__ void k_vox_records(const float *__restrict__ pts, const float *__restrict__ pcov, int64_t n,
+                              float4 *__restrict__ rec) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const float x = pts[i], y = pts[n + i], z = pts[2 * n + i];
+        if (COV) {
+            rec[2 * i] = make_float4(x, y, z, pcov[i]);
+            rec[2 * i + 1] = make_float4(pcov[n + i], pcov[2 * n + i], pcov[3 * n + i], pcov[4 * n + i]);
+        } else {
+            rec[i] = make_float4(x, y, z, 0.f);
         }
     }
 }
@@ -116,12 +193,37 @@ __device__ void jacobi3(double a[9], double w[9]) {
     }
 }
 
+// f(point, record) for the m points of a voxel in order, the records loaded N at a time (two dependent
+// loads each, so a fit waits out m / N round trips instead of m).  Records of HALVES float4.
+template <int N, int HALVES, typename F>
+__device__ __forceinline__ void each_record(const uint32_t *__restrict__ order, const float4 *__restrict__ rec, int m,
+                                            F &&f) {
+#pragma unroll 1
+    for (int j0 = 0; j0 < m; j0 += N) {
+        uint32_t p[N];
+        float4 r[N];
+#pragma unroll
+        for (int q = 0; q < N; q++) p[q] = order[j0 + q < m ? j0 + q : m - 1];
+#pragma unroll
+        for (int q = 0; q < N; q++) r[q] = rec[(int64_t)HALVES * p[q]];
+#pragma unroll
+        for (int q = 0; q < N; q++)
+            if (j0 + q < m) f(p[q], r[q]);
+    }
+}
+
+// One thread per voxel, its sums in the order of the points: the same bits however they are fetched
+// (where eigenvalues coincide the eigenvectors follow the last bit).  Bound by the gather: 6.4M points in
+// random order, 32 per voxel, with covariances take 535 us (and 70 for the records) against 1760 with one component and one
+// point at a time.
+//
 // COV: Eq. 1-2 with the per-point world covariances pcov [6][n] (xx, xy, xz, yy, yz, zz) instead
 // of sigma^2 I; the full descriptor covariance goes to sg [21][n] (upper triangle, row-major)
 // when sg is not null.
 template <bool COV>
-__global__ __launch_bounds__(256) void k_vox_pca(const float *__restrict__ pts, int64_t n, gsr_voxels V, const float *__restrict__ pcov,
-                          float *__restrict__ sg) {
+__global__ __launch_bounds__(64) void k_vox_pca(const float4 *__restrict__ rec, int64_t n, gsr_voxels V,
+                                                const float *__restrict__ pcov, float *__restrict__ sg) {
+    constexpr int kStep = COV ? 2 : 1;
     const uint32_t nv = *V.n_voxels;
     const uint32_t nvalid = (uint32_t)n - *V.n_outside;
     for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
@@ -131,20 +233,19 @@ __global__ __launch_bounds__(256) void k_vox_pca(const float *__restrict__ pts, 
         const int m = cnt < (uint32_t)kMaxPts ? (int)cnt : kMaxPts;
         V.count[v] = cnt;
         double mu[3] = {0, 0, 0};
-        for (int j = 0; j < m; j++) {
-            const uint32_t p = V.point_order[s0 + j];
-            mu[0] += pts[p];
-            mu[1] += pts[n + p];
-            mu[2] += pts[2 * n + p];
-        }
+        const uint32_t *order = V.point_order + s0;
+        each_record<8, kStep>(order, rec, m, [&](uint32_t, const float4 &x) {
+            mu[0] += x.x;
+            mu[1] += x.y;
+            mu[2] += x.z;
+        });
         for (int c = 0; c < 3; c++) mu[c] /= m;
         double C[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int j = 0; j < m; j++) {
-            const uint32_t p = V.point_order[s0 + j];
-            const double d[3] = {pts[p] - mu[0], pts[n + p] - mu[1], pts[2 * n + p] - mu[2]};
+        each_record<8, kStep>(order, rec, m, [&](uint32_t, const float4 &x) {
+            const double d[3] = {x.x - mu[0], x.y - mu[1], x.z - mu[2]};
             for (int a = 0; a < 3; a++)
                 for (int b = 0; b < 3; b++) C[a * 3 + b] += d[a] * d[b];
-        }
+        });
         for (int k = 0; k < 9; k++) C[k] /= m;
         double A[9], W[9];
         for (int k = 0; k < 9; k++) A[k] = C[k];
@@ -200,9 +301,16 @@ __global__ __launch_bounds__(256) void k_vox_pca(const float *__restrict__ pts, 
                 double vk[3], lk = k == 0 ? l[0] : l[2];
 #pragma unroll
                 for (int r = 0; r < 3; r++) vk[r] = k == 0 ? ev[0][r] : ev[2][r];
+                // (one point at a time, the next one's loads in flight: the body is too wide for more)
+                uint32_t p = order[0];
+                float4 x = rec[2 * (int64_t)p], y = rec[2 * (int64_t)p + 1];
+                float zz = pcov[5 * n + p];
+#pragma unroll 1
                 for (int j = 0; j < m; j++) {
-                    const uint32_t p = V.point_order[s0 + j];
-                    const double d[3] = {pts[p] - mu[0], pts[n + p] - mu[1], pts[2 * n + p] - mu[2]};
+                    p = order[j + 1 < m ? j + 1 : j];
+                    const float4 nx = rec[2 * (int64_t)p], ny = rec[2 * (int64_t)p + 1];
+                    const float nzz = pcov[5 * n + p];
+                    const double d[3] = {x.x - mu[0], x.y - mu[1], x.z - mu[2]};
                     const double dk = d[0] * vk[0] + d[1] * vk[1] + d[2] * vk[2];
                     // T = V F = sum_{q != k} v_q f_q^T, f_q = ((d.v_q) v_k + (d.v_k) v_q) / (m (l_k - l_q))
                     double T[9];
@@ -218,9 +326,7 @@ __global__ __launch_bounds__(256) void k_vox_pca(const float *__restrict__ pts, 
 #pragma unroll
                             for (int c = 0; c < 3; c++) T[r * 3 + c] += ev[q][r] * ((dq * vk[c] + dk * ev[q][c]) * inv);
                     }
-                    const double S[9] = {pcov[p],         pcov[n + p],     pcov[2 * n + p],
-                                         pcov[n + p],     pcov[3 * n + p], pcov[4 * n + p],
-                                         pcov[2 * n + p], pcov[4 * n + p], pcov[5 * n + p]};
+                    const double S[9] = {x.w, y.x, y.y, y.x, y.z, y.w, y.y, y.w, zz};
                     // J = [T; I/m] (6 x 3), G += J S J^T
                     double J[6][3], JS[6][3];
 #pragma unroll
@@ -236,6 +342,7 @@ __global__ __launch_bounds__(256) void k_vox_pca(const float *__restrict__ pts, 
 #pragma unroll
                         for (int c = r; c < 6; c++)
                             G[r * 6 - r * (r - 1) / 2 + (c - r)] += JS[r][0] * J[c][0] + JS[r][1] * J[c][1] + JS[r][2] * J[c][2];
+                    x = nx, y = ny, zz = nzz;
                 }
                 tr = G[0] + G[6] + G[11];  // (0,0), (1,1), (2,2) of the upper triangle
             }
@@ -260,20 +367,26 @@ __global__ __launch_bounds__(256) void k_vox_pca(const float *__restrict__ pts, 
 
 using namespace gsr;
 
-extern "C" gsr_status gsr_scan_launch(const uint32_t *, int64_t, uint32_t *, uint32_t *, void *, hipStream_t);
-extern "C" size_t gsr_scan_ws_bytes(int64_t n);
+extern "C" gsr_status gsr_exclusive_scan_small_launch(uint32_t *, int, uint32_t *, hipStream_t);
 extern "C" size_t gsr_sort_pairs_ws_bytes(int64_t n);
 extern "C" gsr_status gsr_sort_pairs_launch(uint32_t *, uint32_t *, uint32_t *, uint32_t *, uint32_t, int, void *,
                                             hipStream_t);
+extern "C" gsr_status gsr_sort_positions_launch(uint32_t *k[2], uint32_t *v[2], uint32_t *w[2], uint32_t n, int bits,
+                                                void *ws, hipStream_t st);
 extern "C" gsr_status gsr_fill_u32_launch(void *, uint32_t, int64_t, hipStream_t);
 
 namespace {
+// rec takes the place of the sort's arrays once the points are in order
 struct VoxWs {
-    uint32_t *key, *hhi, *k0, *v0, *k1, *v1, *head, *hscan;
-    void *sort_ws, *scan_ws;
+    float4 *rec;  // [2 n]
+    uint32_t *k[2], *h[2], *i[2], *bsum;
+    void *sort_ws;
     size_t bytes;
 };
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
+// points per numbering block: 1,024 fill the chip sooner (a block of 4,096 took 29 us at 100k points, a
+// quarter of that 12), 4,096 keep the block sums few enough to be added up by their readers
+int64_t vox_tile(int64_t n) { return n <= (1 << 20) ? 1024 : 4096; }
 VoxWs vox_layout(void *base, int64_t n) {
     VoxWs w{};
     char *p = static_cast<char *>(base);
@@ -284,16 +397,15 @@ VoxWs vox_layout(void *base, int64_t n) {
         return r;
     };
     const size_t nb = (size_t)(n > 0 ? n : 1) * 4;
-    w.key = (uint32_t *)take(nb);
-    w.hhi = (uint32_t *)take(nb);
-    w.k0 = (uint32_t *)take(nb);
-    w.v0 = (uint32_t *)take(nb);
-    w.k1 = (uint32_t *)take(nb);
-    w.v1 = (uint32_t *)take(nb);
-    w.head = (uint32_t *)take(nb);
-    w.hscan = (uint32_t *)take(nb);
+    for (int q = 0; q < 2; q++) {
+        w.k[q] = (uint32_t *)take(nb);
+        w.h[q] = (uint32_t *)take(nb);
+        w.i[q] = (uint32_t *)take(nb);
+    }
+    w.rec = (float4 *)w.k[0];
+    if (off < 8 * nb) take(8 * nb - off);
     w.sort_ws = take(gsr_sort_pairs_ws_bytes(n));
-    w.scan_ws = take(gsr_scan_ws_bytes(n));
+    w.bsum = (uint32_t *)take((size_t)ceil_div(n > 0 ? n : 1, vox_tile(n)) * 4);
     w.bytes = off;
     return w;
 }
@@ -304,28 +416,42 @@ extern "C" size_t gsr_voxel_pca_ws_bytes(int64_t n) { return vox_layout(nullptr,
 
 static gsr_status voxel_pca_run(const float *pts, int64_t n, uint64_t seed, const gsr_voxels *out, void *ws,
                                 hipStream_t st, const float *pcov, float *sg) {
-    gsr_status s = gsr_fill_u32_launch(out->n_outside, 0u, 1, st);
-    if (s != GSR_OK) return s;
-    if (n == 0) return gsr_fill_u32_launch(out->n_voxels, 0u, 1, st);
+    if (n == 0) {
+        gsr_status s = gsr_fill_u32_launch(out->n_outside, 0u, 1, st);
+        return s != GSR_OK ? s : gsr_fill_u32_launch(out->n_voxels, 0u, 1, st);
+    }
     VoxWs w = vox_layout(ws, n);
     const int g = grid(n);
-    k_vox_prep<<<g, 256, 0, st>>>(pts, n, seed, w.key, w.k0, w.hhi, w.v0);
-    // (hash low, hash high, voxel key): three stable sorts, least significant first; each of
-    // 4 passes, so the result lands back in (k0, v0)
-    s = gsr_sort_pairs_launch(w.k0, w.v0, w.k1, w.v1, (uint32_t)n, 32, w.sort_ws, st);
+    // Leading hash bits sorted on: with 16, points of one voxel that agree in them are rare (1 in 130
+    // voxels of 32 points holds two), and a run of them averages n / 2^16 points even if all points lie in
+    // one voxel; beyond 2^24 points that bound asks for 24.  Two passes and the key's four instead of
+    // twelve (the whole hash, then the key).
+    const int hash_bits = n <= (1 << 24) ? 16 : 24;
+    k_vox_prep<<<g, 256, 0, st>>>(pts, n, seed, hash_bits, w.k[0], w.h[0], out->n_outside);
+    gsr_status s = gsr_sort_positions_launch(w.h, w.k, w.i, (uint32_t)n, hash_bits, w.sort_ws, st);
     if (s != GSR_OK) return s;
-    k_gather_u32<<<g, 256, 0, st>>>(w.hhi, w.v0, n, w.k0);
-    s = gsr_sort_pairs_launch(w.k0, w.v0, w.k1, w.v1, (uint32_t)n, 32, w.sort_ws, st);
+    // four passes: the result lands back in (k[0], i[0])
+    s = gsr_sort_pairs_launch(w.k[0], w.i[0], w.k[1], w.i[1], (uint32_t)n, 32, w.sort_ws, st);
     if (s != GSR_OK) return s;
-    k_gather_u32<<<g, 256, 0, st>>>(w.key, w.v0, n, w.k0);
-    s = gsr_sort_pairs_launch(w.k0, w.v0, w.k1, w.v1, (uint32_t)n, 32, w.sort_ws, st);
-    if (s != GSR_OK) return s;
-    k_vox_heads<<<g, 256, 0, st>>>(w.k0, n, w.head);
-    s = gsr_scan_launch(w.head, n, w.hscan, out->n_voxels, w.scan_ws, st);
-    if (s != GSR_OK) return s;
-    k_vox_assign<<<g, 256, 0, st>>>(w.k0, w.v0, w.head, w.hscan, n, *out);
-    if (pcov) k_vox_pca<true><<<g, 256, 0, st>>>(pts, n, *out, pcov, sg);
-    else k_vox_pca<false><<<g, 256, 0, st>>>(pts, n, *out, nullptr, nullptr);
+    const int nb = (int)ceil_div(n, vox_tile(n));
+    const bool scanned = nb > 2048, few = vox_tile(n) == 1024;
+    if (few) k_vox_heads<4><<<nb, 256, 0, st>>>(w.k[0], n, w.bsum);
+    else k_vox_heads<16><<<nb, 256, 0, st>>>(w.k[0], n, w.bsum);
+    if (scanned) {
+        s = gsr_exclusive_scan_small_launch(w.bsum, nb, out->n_voxels, st);
+        if (s != GSR_OK) return s;
+    }
+    if (few) k_vox_assign<4><<<nb, 256, 0, st>>>(w.k[0], w.i[0], n, seed, hash_bits, w.bsum, scanned, *out);
+    else k_vox_assign<16><<<nb, 256, 0, st>>>(w.k[0], w.i[0], n, seed, hash_bits, w.bsum, scanned, *out);
+    const int64_t fits = ceil_div(n, 64);
+    const int gf = (int)(fits < 16384 ? fits : 16384);
+    if (pcov) {
+        k_vox_records<true><<<g, 256, 0, st>>>(pts, pcov, n, w.rec);
+        k_vox_pca<true><<<gf, 64, 0, st>>>(w.rec, n, *out, pcov, sg);
+    } else {
+        k_vox_records<false><<<g, 256, 0, st>>>(pts, nullptr, n, w.rec);
+        k_vox_pca<false><<<gf, 64, 0, st>>>(w.rec, n, *out, nullptr, nullptr);
+    }
     return last_launch();
 }
 
@@ -363,41 +489,6 @@ __device__ __forceinline__ bool pred_valid(const float *pred, int64_t stride, ui
     return true;
 }
 
-// Per-segment point counts for beta.  Points of one segment arrive together, so per-point global
-// atomics would all hit one address; each workgroup counts in LDS (up to kSegLds segments) and
-// adds its totals once.
-constexpr int kSegLds = 1024;
-
-__global__ __launch_bounds__(256) void k_seg_counts(const uint32_t *__restrict__ pvox,
-                                                    const uint8_t *__restrict__ reliable, const float *__restrict__ pred,
-                                                    int64_t n, const int32_t *__restrict__ seg, int nseg,
-                                                    uint32_t *__restrict__ cnt, uint32_t *__restrict__ fb) {
-    __shared__ uint32_t s_cnt[kSegLds], s_fb[kSegLds];
-    const bool lds = nseg <= kSegLds;
-    if (lds)
-        for (int e = threadIdx.x; e < nseg; e += 256) s_cnt[e] = s_fb[e] = 0u;
-    __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t v = pvox[i];
-        const int s = seg ? seg[i] : 0;
-        if (v == kOutside || s < 0 || s >= nseg) continue;
-        const bool f = reliable[v] && !pred_valid(pred, n, v);
-        if (lds) {
-            atomicAdd(&s_cnt[s], 1u);
-            if (f) atomicAdd(&s_fb[s], 1u);
-        } else {
-            atomicAdd(&cnt[s], 1u);
-            if (f) atomicAdd(&fb[s], 1u);
-        }
-    }
-    __syncthreads();
-    if (lds)
-        for (int e = threadIdx.x; e < nseg; e += 256) {
-            if (s_cnt[e]) atomicAdd(&cnt[e], s_cnt[e]);
-            if (s_fb[e]) atomicAdd(&fb[e], s_fb[e]);
-        }
-}
-
 // rotation matrix (row-major) -> unit quaternion (w, x, y, z), w >= 0, largest-pivot method
 __device__ void rot_to_quat(const double r[9], double q[4]) {
     const double tr = r[0] + r[4] + r[8];
@@ -419,37 +510,150 @@ __device__ void rot_to_quat(const double r[9], double q[4]) {
     for (int k = 0; k < 4; k++) q[k] = sg * q[k] / nq;
 }
 
+// What Eq. 3 takes from a voxel, the same for all its points: the branch (0 model, 1 PCA, 2 heuristic)
+// and for the first two the log-scales before their per-point or per-segment shift (Eq. 4's axis
+// ratios when anchored), the quaternion and the model's opacity logit.
+struct VoxInit {
+    float ls[3], lo, q[4];
+};
+
+__device__ __forceinline__ uint8_t voxel_init(const gsr_voxels &V, const float *__restrict__ pred, int64_t n, uint32_t v,
+                                              int anchored, VoxInit &o) {
+    if (pred_valid(pred, n, v)) {
+        float nq = 0.f;
+        for (int k = 0; k < 4; k++) nq += pred[(3 + k) * n + v] * pred[(3 + k) * n + v];
+        nq = sqrtf(nq);
+        for (int k = 0; k < 3; k++) o.ls[k] = pred[k * n + v];
+        if (anchored) {
+            const float mx = fmaxf(o.ls[0], fmaxf(o.ls[1], o.ls[2]));
+            for (int k = 0; k < 3; k++) o.ls[k] -= mx;
+        }
+        for (int k = 0; k < 4; k++) o.q[k] = pred[(3 + k) * n + v] / nq;
+        o.lo = pred[7 * n + v];
+        return 0;
+    }
+    if (V.reliable[v]) {
+        for (int k = 0; k < 3; k++) o.ls[k] = V.s_pca[k * n + v];
+        double r[9], qd[4];
+        for (int k = 0; k < 9; k++) r[k] = V.R[k * n + v];
+        rot_to_quat(r, qd);
+        for (int k = 0; k < 4; k++) o.q[k] = (float)qd[k];
+        o.lo = 0.f;
+        return 1;
+    }
+    return 2;
+}
+
+// Every voxel's VoxInit, computed once instead of once per point, in the sh output (written last, by
+// k_cascade_sh): records, then branch bytes.  There is room unless the voxels hold very few points
+// (sh holds 3 K floats per point); `table` decides on the device, where the voxel count is.  A point
+// then gathers one byte and one 32-byte record where it gathered some twenty values and formed a
+// quaternion in FP64: 6.4M points of 200k voxels in random order, 162 us and 34 for the table and the sh output (827 before), and
+// the segment counts 39 (228).
+struct CascadeTable {
+    VoxInit *rec;  // null: no table (the sh output overlaps an input, or is not 16-byte aligned)
+    int64_t floats;  // of the sh output
+    __device__ __forceinline__ bool on(uint32_t nv) const { return rec && (int64_t)nv * 8 + (nv + 3) / 4 <= floats; }
+    __device__ __forceinline__ uint8_t *branch(uint32_t nv) const { return reinterpret_cast<uint8_t *>(rec + nv); }
+};
+
+__global__ __launch_bounds__(256) void k_cascade_voxels(gsr_voxels V, const float *__restrict__ pred, int64_t n,
+                                                        int anchored, CascadeTable T) {
+    const uint32_t nv = *V.n_voxels;
+    if (!T.on(nv)) return;
+    for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < nv; v += gridDim.x * 256) {
+        VoxInit o;
+        const uint8_t br = voxel_init(V, pred, n, v, anchored, o);
+        T.branch(nv)[v] = br;
+        if (br == 2) continue;
+        float4 *r = reinterpret_cast<float4 *>(T.rec + v);
+        r[0] = make_float4(o.ls[0], o.ls[1], o.ls[2], o.lo);
+        r[1] = make_float4(o.q[0], o.q[1], o.q[2], o.q[3]);
+    }
+}
+
+// Per-segment point counts for beta.  Points of one segment arrive together, so per-point global
+// atomics would all hit one address; each workgroup counts in LDS (up to kSegLds segments), a wave
+// whose points share a segment in one add, and adds its totals once.
+constexpr int kSegLds = 1024;
+
+__global__ __launch_bounds__(256) void k_seg_counts(const uint32_t *__restrict__ pvox, gsr_voxels V,
+                                                    const float *__restrict__ pred, int64_t n,
+                                                    const int32_t *__restrict__ seg, int nseg, CascadeTable T,
+                                                    uint32_t *__restrict__ cnt, uint32_t *__restrict__ fb) {
+    __shared__ uint32_t s_cnt[kSegLds], s_fb[kSegLds];
+    const bool lds = nseg <= kSegLds;
+    if (lds)
+        for (int e = threadIdx.x; e < nseg; e += 256) s_cnt[e] = s_fb[e] = 0u;
+    __syncthreads();
+    const uint32_t nv = *V.n_voxels;
+    const bool table = T.on(nv);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t v = pvox[i];
+        const int s = seg ? seg[i] : 0;
+        if (v == kOutside || s < 0 || s >= nseg) continue;
+        const bool f = table ? T.branch(nv)[v] == 1 : V.reliable[v] && !pred_valid(pred, n, v);
+        uint32_t *c = lds ? s_cnt : cnt, *b = lds ? s_fb : fb;
+        const uint64_t here = __ballot(true), fall = __ballot(f);
+        if (__ballot(s == __builtin_amdgcn_readfirstlane(s)) == here) {
+            if (__lane_id() == __builtin_ctzll(here)) {
+                atomicAdd(&c[s], (uint32_t)__popcll(here));
+                if (fall) atomicAdd(&b[s], (uint32_t)__popcll(fall));
+            }
+        } else {
+            atomicAdd(&c[s], 1u);
+            if (f) atomicAdd(&b[s], 1u);
+        }
+    }
+    __syncthreads();
+    if (lds)
+        for (int e = threadIdx.x; e < nseg; e += 256) {
+            if (s_cnt[e]) atomicAdd(&cnt[e], s_cnt[e]);
+            if (s_fb[e]) atomicAdd(&fb[e], s_fb[e]);
+        }
+}
+
+__device__ __forceinline__ void write_sh(const float *__restrict__ col, int64_t n, int64_t i, int K, float *__restrict__ sh) {
+    for (int c = 0; c < 3; c++) sh[c * n + i] = (col[c * n + i] - 0.5f) / kY00;
+    for (int k = 3; k < 3 * K; k++) sh[k * n + i] = 0.f;
+}
+
 __global__ void k_cascade(const float *__restrict__ pts, const float *__restrict__ col, const float *__restrict__ depth,
                           const int32_t *__restrict__ seg, int nseg, int64_t n, gsr_voxels V,
                           const float *__restrict__ pred, float focal, float beta_fixed,
-                          const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ fb, int K, gsr_params out,
-                          uint8_t *__restrict__ branch, int anchored) {
+                          const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ fb, int K, CascadeTable T,
+                          gsr_params out, uint8_t *__restrict__ branch, int anchored) {
+    const uint32_t nv = *V.n_voxels;
+    const bool table = T.on(nv);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t v = V.point_voxel[i];
-        for (int c = 0; c < 3; c++) {
-            out.means[c * n + i] = pts[c * n + i];
-            out.sh[c * n + i] = (col[c * n + i] - 0.5f) / kY00;
+        for (int c = 0; c < 3; c++) out.means[c * n + i] = pts[c * n + i];
+        if (!table) write_sh(col, n, i, K, out.sh);
+        VoxInit o;
+        uint8_t br = 2;
+        if (v != kOutside) {
+            if (!table) {
+                br = voxel_init(V, pred, n, v, anchored, o);
+            } else {
+                br = T.branch(nv)[v];
+                if (br != 2) {
+                    const float4 *r = reinterpret_cast<const float4 *>(T.rec + v);
+                    const float4 a = r[0], q = r[1];
+                    o = VoxInit{{a.x, a.y, a.z}, a.w, {q.x, q.y, q.z, q.w}};
+                }
+            }
         }
-        for (int k = 3; k < 3 * K; k++) out.sh[k * n + i] = 0.f;
-        const bool inside = v != kOutside;
-        const bool valid = inside && pred_valid(pred, n, v);
-        const bool rel = inside && V.reliable[v];
-        const uint8_t br = valid ? 0 : (rel ? 1 : 2);
         branch[i] = br;
-        float ls[3], q[4], lo = logf(kOpacityConst / (1.f - kOpacityConst));
+        float ls[3], q[4] = {1.f, 0.f, 0.f, 0.f}, lo = logf(kOpacityConst / (1.f - kOpacityConst));
         if (br == 0) {
-            float nq = 0.f;
-            for (int k = 0; k < 4; k++) nq += pred[(3 + k) * n + v] * pred[(3 + k) * n + v];
-            nq = sqrtf(nq);
-            for (int k = 0; k < 3; k++) ls[k] = pred[k * n + v];
+            for (int k = 0; k < 3; k++) ls[k] = o.ls[k];
             if (anchored) {
                 // Eq. 4: keep the axis ratios a = exp(s - max s) and anchor the size at d / f
-                const float mx = fmaxf(ls[0], fmaxf(ls[1], ls[2]));
                 const float a0 = logf(depth[i] / focal);
-                for (int k = 0; k < 3; k++) ls[k] = a0 + (ls[k] - mx);
+                for (int k = 0; k < 3; k++) ls[k] = a0 + o.ls[k];
             }
-            for (int k = 0; k < 4; k++) q[k] = pred[(3 + k) * n + v] / nq;
-            lo = pred[7 * n + v];
+            for (int k = 0; k < 4; k++) q[k] = o.q[k];
+            lo = o.lo;
         } else if (br == 1) {
             float beta = beta_fixed;
             if (!(beta > 0.f)) {
@@ -459,20 +663,23 @@ __global__ void k_cascade(const float *__restrict__ pts, const float *__restrict
                 beta = fminf(fmaxf(1.f - rho, 0.5f), 1.f);
             }
             const float lb = logf(beta);
-            for (int k = 0; k < 3; k++) ls[k] = V.s_pca[k * n + v] + lb;
-            double r[9], qd[4];
-            for (int k = 0; k < 9; k++) r[k] = V.R[k * n + v];
-            rot_to_quat(r, qd);
-            for (int k = 0; k < 4; k++) q[k] = (float)qd[k];
+            for (int k = 0; k < 3; k++) ls[k] = o.ls[k] + lb;
+            for (int k = 0; k < 4; k++) q[k] = o.q[k];
         } else {
             const float s = logf(depth[i] / focal);
             ls[0] = ls[1] = ls[2] = s;
-            q[0] = 1.f, q[1] = q[2] = q[3] = 0.f;
         }
         for (int k = 0; k < 3; k++) out.log_scales[k * n + i] = ls[k];
         for (int k = 0; k < 4; k++) out.quats[k * n + i] = q[k];
         out.opacity_logits[i] = lo;
     }
+}
+
+__global__ void k_cascade_sh(const float *__restrict__ col, int64_t n, gsr_voxels V, int K, CascadeTable T,
+                             float *__restrict__ sh) {
+    if (!T.on(*V.n_voxels)) return;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        write_sh(col, n, i, K, sh);
 }
 
 // Training targets of the point network (Sec. III-B): for every voxel, the mean covariance
@@ -524,10 +731,25 @@ extern "C" gsr_status gsr_cascade_launch(const float *pts, const float *col, con
     uint32_t *fb = cnt + (nseg > 0 ? nseg : 1);
     gsr_status s = gsr_fill_u32_launch(cnt, 0u, 2 * (int64_t)(nseg > 0 ? nseg : 1), st);
     if (s != GSR_OK) return s;
-    const int g = grid(n);
-    k_seg_counts<<<g < 1024 ? g : 1024, 256, 0, st>>>(vox->point_voxel, vox->reliable, pred, n, seg, nseg, cnt, fb);
-    k_cascade<<<g, 256, 0, st>>>(pts, col, depth, seg, nseg, n, *vox, pred, focal, beta, cnt, fb,
-                                 (sh_degree + 1) * (sh_degree + 1), *out, branch, anchored);
+    const int g = grid(n), K = (sh_degree + 1) * (sh_degree + 1);
+    // the sh output holds the voxel table until it is written, unless it shares memory with something
+    // read or written before that (a caller may convert colours in place)
+    CascadeTable T{reinterpret_cast<VoxInit *>(out->sh), 3 * (int64_t)K * n};
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(out->sh), hi = lo + (uintptr_t)T.floats * 4;
+    auto clash = [&](const void *p, int64_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        return p && a < hi && a + (uintptr_t)bytes > lo;
+    };
+    if ((lo & 15) || clash(pts, 12 * n) || clash(col, 12 * n) || clash(depth, 4 * n) || clash(seg, 4 * n) ||
+        clash(pred, 32 * n) || clash(vox->point_voxel, 4 * n) || clash(vox->reliable, n) || clash(vox->s_pca, 12 * n) ||
+        clash(vox->R, 36 * n) || clash(vox->n_voxels, 4) || clash(out->means, 12 * n) || clash(out->log_scales, 12 * n) ||
+        clash(out->quats, 16 * n) || clash(out->opacity_logits, 4 * n) || clash(branch, n) || clash(ws, gsr_cascade_ws_bytes(nseg)))
+        T.rec = nullptr;
+    if (T.rec) k_cascade_voxels<<<g < 1024 ? g : 1024, 256, 0, st>>>(*vox, pred, n, anchored, T);
+    k_seg_counts<<<g < 1024 ? g : 1024, 256, 0, st>>>(vox->point_voxel, *vox, pred, n, seg, nseg, T, cnt, fb);
+    k_cascade<<<g, 256, 0, st>>>(pts, col, depth, seg, nseg, n, *vox, pred, focal, beta, cnt, fb, K, T, *out, branch,
+                                 anchored);
+    if (T.rec) k_cascade_sh<<<g, 256, 0, st>>>(col, n, *vox, K, T, out->sh);
     return last_launch();
 }
 
