@@ -14,7 +14,11 @@ __global__ void k_zero_f32(float *__restrict__ dst, int64_t n) {
 // Small pairs (at most kSmallPair records): each wave takes 64 consecutive visible pairs in
 // emission order.  Their records form one contiguous run, which the wave streams through LDS
 // kWinRecs records at a time with coalesced loads (a window that holds no record of a small pair
-// is not loaded), and each lane adds its own pair's records from there, in order.
+// is not loaded), and each lane adds its own pair's records from there, in order.  With few pairs
+// (kFewPairs) that leaves SIMDs idle behind long chains, and a wave takes 16 pairs, four lanes each with
+// a part of the components (the order of every component's additions stays): 40k pairs with 600k
+// records 65 -> 18 us.  With 2.8M pairs the chip is full either way and the launch is bound by its
+// 0.8 GB (215 us).
 // Large pairs (near Gaussians cover hundreds of tiles, and depth order puts them first): each is
 // summed by one whole wave, each lane striding over the records and a lane tree adding the 64
 // partial sums.  The large pairs are dealt out across the grid: lane l of wave w looks at pair
@@ -23,6 +27,7 @@ __global__ void k_zero_f32(float *__restrict__ dst, int64_t n) {
 // data, so the result repeats exactly.
 constexpr uint32_t kSmallPair = 64;
 constexpr int kPairWaves = 4;  // waves per workgroup
+constexpr int64_t kFewPairs = 1 << 20;  // (view, Gaussian) pairs, visible or not
 constexpr int kWinRecs = 256;  // records per LDS window of a wave
 
 __device__ __forceinline__ uint32_t pair_count(const uint32_t *__restrict__ pair_gid,
@@ -33,36 +38,39 @@ __device__ __forceinline__ uint32_t pair_count(const uint32_t *__restrict__ pair
     return q + 1 < np ? pair_first[q + 1] - first : ntiles[pair_gid[q]];
 }
 
+// LPP: lanes per small pair (1 or 4)
+template <int LPP>
 __global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__restrict__ dinst,
                                                                 const uint32_t *__restrict__ pair_gid,
                                                                 const uint32_t *__restrict__ pair_first,
                                                                 const uint32_t *__restrict__ n_pairs,
                                                                 const uint32_t *__restrict__ ntiles,
                                                                 float *__restrict__ dsplat) {
-    // one window of records per wave: floats 0-3 and 4-7 of each record as float4, 8-9 as float2
-    __shared__ float4 s_w4[kPairWaves][2][kWinRecs];
-    __shared__ float2 s_w2[kPairWaves][kWinRecs];
+    // one window of records per wave: floats 0-3, 4-7 and 8-9 of each record, as float4
+    __shared__ float4 s_w4[kPairWaves][3][kWinRecs];
     const uint32_t np = *n_pairs;
     const int lane = __lane_id();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    float4 *const w4a = s_w4[threadIdx.x >> 6][0], *const w4b = s_w4[threadIdx.x >> 6][1];
-    float2 *const w2 = s_w2[threadIdx.x >> 6];
+    float4(*const win)[kWinRecs] = s_w4[threadIdx.x >> 6];
     // small pairs, one per lane
-    for (uint32_t w0 = gw * 64; w0 < np; w0 += nwaves * 64) {
-        const uint32_t q = w0 + lane;
+    constexpr uint32_t kPer = 64 / LPP;
+    constexpr int kParts = LPP == 1 ? 3 : 1;  // float4 parts of a record per lane
+    const uint32_t sub = lane % LPP, part = sub < 3 ? sub : 2;
+    for (uint32_t w0 = gw * kPer; w0 < np; w0 += nwaves * kPer) {
+        const uint32_t q = w0 + lane / LPP;
         const bool live = q < np;
         const uint32_t first = live ? pair_first[q] : 0u;
         const uint32_t cnt = live ? pair_count(pair_gid, pair_first, ntiles, q, np, first) : 0u;
         const bool small = live && cnt <= kSmallPair;
         // the run of records of the wave's pairs: from the first pair's first record to the end
         // of the last live pair
-        const int lastl = np - w0 < 64u ? (int)(np - w0) - 1 : 63;
+        const int lastl = np - w0 < kPer ? (int)(np - w0 - 1) * LPP : 63;
         const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
         const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)(first + cnt), lastl);
-        float acc[GSR_SPLAT_GRAD_FLOATS];
+        float acc[4 * kParts];
 #pragma unroll
-        for (int e = 0; e < GSR_SPLAT_GRAD_FLOATS; e++) acc[e] = 0.f;
+        for (int e = 0; e < 4 * kParts; e++) acc[e] = 0.f;
         for (uint32_t a = r0; a < r1; a += kWinRecs) {
             // this lane's records inside the window [a, a + kWinRecs)
             const uint32_t k0 = first > a ? first : a;
@@ -82,33 +90,33 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__r
             for (int u = 0; u < kWinRecs / 64; u++)
                 if (a + u * 64 + lane < r1) {
                     const int s = u * 64 + lane;
-                    w4a[s] = make_float4(x[u][0].x, x[u][0].y, x[u][1].x, x[u][1].y);
-                    w4b[s] = make_float4(x[u][2].x, x[u][2].y, x[u][3].x, x[u][3].y);
-                    w2[s] = x[u][4];
+                    win[0][s] = make_float4(x[u][0].x, x[u][0].y, x[u][1].x, x[u][1].y);
+                    win[1][s] = make_float4(x[u][2].x, x[u][2].y, x[u][3].x, x[u][3].y);
+                    win[2][s] = make_float4(x[u][4].x, x[u][4].y, 0.f, 0.f);
                 }
             __builtin_amdgcn_wave_barrier();  // the wave reads back what its lanes just wrote
             if (need)
                 for (uint32_t k = k0; k < k1; k++) {
-                    const int s = (int)(k - a);
-                    const float4 xa = w4a[s], xb = w4b[s];
-                    const float2 xc = w2[s];
-                    acc[0] += xa.x;
-                    acc[1] += xa.y;
-                    acc[2] += xa.z;
-                    acc[3] += xa.w;
-                    acc[4] += xb.x;
-                    acc[5] += xb.y;
-                    acc[6] += xb.z;
-                    acc[7] += xb.w;
-                    acc[8] += xc.x;
-                    acc[9] += xc.y;
+#pragma unroll
+                    for (int p = 0; p < kParts; p++) {
+                        const float4 x4 = win[LPP == 1 ? p : part][k - a];
+                        acc[4 * p] += x4.x;
+                        acc[4 * p + 1] += x4.y;
+                        acc[4 * p + 2] += x4.z;
+                        acc[4 * p + 3] += x4.w;
+                    }
                 }
             __builtin_amdgcn_wave_barrier();  // every read of the window precedes the next window's writes
         }
         if (small) {
             float2 *out = reinterpret_cast<float2 *>(dsplat + (int64_t)pair_gid[q] * GSR_SPLAT_GRAD_FLOATS);
+            if (LPP == 1) {
 #pragma unroll
-            for (int e = 0; e < 5; e++) out[e] = make_float2(acc[2 * e], acc[2 * e + 1]);
+                for (int e = 0; e < 5; e++) out[e] = make_float2(acc[2 * e], acc[2 * e + 1]);
+            } else if (sub < 3) {
+                out[2 * sub] = make_float2(acc[0], acc[1]);
+                if (sub < 2) out[2 * sub + 1] = make_float2(acc[2], acc[3]);
+            }
         }
     }
     // large pairs, one per wave, dealt out across the grid
@@ -129,6 +137,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__r
             float acc[GSR_SPLAT_GRAD_FLOATS];
 #pragma unroll
             for (int e = 0; e < GSR_SPLAT_GRAD_FLOATS; e++) acc[e] = 0.f;
+#pragma unroll 4
             for (uint32_t j = lane; j < bc; j += 64) {
                 const float2 *rec =
                     reinterpret_cast<const float2 *>(dinst + ((int64_t)bf + j) * GSR_SPLAT_GRAD_FLOATS);
@@ -163,8 +172,11 @@ extern "C" gsr_status gsr_pair_grads_launch(const float *dinst, const gsr_emissi
         const int nz = (int)(ceil_div(words, 256) < 16384 ? ceil_div(words, 256) : 16384);
         k_zero_f32<<<nz, 256, 0, st>>>(dsplat, words);
     }
-    const int nb = (int)(ceil_div(VN, 64 * kPairWaves) < 8192 ? ceil_div(VN, 64 * kPairWaves) : 8192);
-    k_pair_grads<<<nb, 64 * kPairWaves, 0, st>>>(dinst, em->pair_gid, em->pair_first, em->n_pairs, tile_info, dsplat);
+    const bool few = VN <= kFewPairs;
+    const int64_t want = ceil_div(VN, (few ? 16 : 64) * kPairWaves);
+    const int nb = (int)(want < 8192 ? want : 8192);
+    const auto kernel = few ? k_pair_grads<4> : k_pair_grads<1>;
+    kernel<<<nb, 64 * kPairWaves, 0, st>>>(dinst, em->pair_gid, em->pair_first, em->n_pairs, tile_info, dsplat);
     return last_launch();
 }
 
