@@ -271,6 +271,42 @@ __global__ void k_slice_emit(uint32_t *__restrict__ ns, const uint32_t *__restri
     }
 }
 
+// Both and the scan between them for at most kListTiles view-tiles, in one workgroup: five launches of 2 us
+// each on lists that are mostly empty become one.
+constexpr uint32_t kListTiles = 8192;
+__global__ __launch_bounds__(1024) void k_slice_list(const uint32_t *__restrict__ ranges, uint32_t VT, uint32_t cap,
+                                                     uint32_t *__restrict__ ns, uint2 *__restrict__ info,
+                                                     uint32_t *__restrict__ count) {
+    __shared__ uint32_t s_w[16];
+    uint32_t n[kListTiles / 1024];
+#pragma unroll
+    for (uint32_t r = 0; r < kListTiles / 1024; r++) {
+        const uint32_t i = r * 1024 + threadIdx.x;
+        const uint32_t len = i < VT ? ranges[2 * i + 1] - ranges[2 * i] : 0u;
+        n[r] = len > kSplitMin ? (len + kSliceLen - 1) / kSliceLen : 0u;
+    }
+    uint32_t run = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kListTiles / 1024; r++) {
+        if (r * 1024 >= VT) break;
+        const uint32_t i = r * 1024 + threadIdx.x;
+        const uint32_t inc = wave_incl_scan(n[r]);
+        if (__lane_id() == 63) s_w[threadIdx.x >> 6] = inc;
+        __syncthreads();
+        uint32_t off = run + inc - n[r];
+#pragma unroll
+        for (uint32_t w = 0; w < 16; w++) {
+            off += w < threadIdx.x >> 6 ? s_w[w] : 0u;
+            run += s_w[w];
+        }
+        __syncthreads();
+        if (i < VT) ns[i] = off + n[r] > cap ? 0u : n[r];
+        for (uint32_t q = 0; q < n[r] && off + q < cap; q++)
+            info[off + q] = off + n[r] > cap ? make_uint2(kNoSlice, 0u) : make_uint2(i, q);
+    }
+    if (threadIdx.x == 0) *count = run;
+}
+
 // This pixel's product of (1 - a) over slice j, in sub-slice order.
 __device__ __forceinline__ float slice_prod(const SliceArgs &sl, uint32_t j) {
     float P = 1.0f;
@@ -1338,6 +1374,19 @@ SliceWs slice_layout(void *base, int64_t VT, int64_t capacity) {
     return w;
 }
 
+gsr_status list_slices(const uint32_t *ranges, int nb, const SliceWs &w, hipStream_t st) {
+    if (nb <= (int)kListTiles) {
+        k_slice_list<<<1, 1024, 0, st>>>(ranges, (uint32_t)nb, w.cap, w.tile_slices, w.info, w.count);
+        return last_launch();
+    }
+    const int g = (int)(ceil_div(nb, 256) < 1024 ? ceil_div(nb, 256) : 1024);
+    k_slice_count<<<g, 256, 0, st>>>(ranges, (uint32_t)nb, w.tile_slices);
+    const gsr_status s = gsr_scan_launch(w.tile_slices, nb, w.off, w.count, w.scan, st);
+    if (s != GSR_OK) return s;
+    k_slice_emit<<<g, 256, 0, st>>>(w.tile_slices, w.off, (uint32_t)nb, w.cap, w.info);
+    return last_launch();
+}
+
 }  // namespace
 
 extern "C" size_t gsr_render_fwd_ws_bytes(int V, const gsr_raster *r, int64_t capacity) {
@@ -1358,11 +1407,8 @@ extern "C" gsr_status gsr_render_fwd_launch(const gsr_splat *splats, const uint3
     SliceArgs sl{};
     if (ws) {
         const SliceWs w = slice_layout(ws, nb, capacity);
-        const int g = (int)(ceil_div(nb, 256) < 1024 ? ceil_div(nb, 256) : 1024);
-        k_slice_count<<<g, 256, 0, st>>>(ranges, (uint32_t)nb, w.tile_slices);
-        gsr_status s = gsr_scan_launch(w.tile_slices, nb, w.off, w.count, w.scan, st);
+        const gsr_status s = list_slices(ranges, nb, w, st);
         if (s != GSR_OK) return s;
-        k_slice_emit<<<g, 256, 0, st>>>(w.tile_slices, w.off, (uint32_t)nb, w.cap, w.info);
         sl = SliceArgs{w.tile_slices, w.info, w.count, w.tprod, w.part, w.part2, w.cap,
                        w.cap < 2048u ? w.cap : 2048u};
     }
@@ -1419,11 +1465,8 @@ extern "C" gsr_status gsr_render_step_launch(const gsr_splat *splats, const uint
     const SliceWs w = slice_layout(ws, nb, capacity);
     double *item_loss = reinterpret_cast<double *>(static_cast<char *>(ws) + w.bytes);
     uint32_t *counters = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + w.bytes + al256((size_t)nb * 8));
-    const int g = (int)(ceil_div(nb, 256) < 1024 ? ceil_div(nb, 256) : 1024);
-    k_slice_count<<<g, 256, 0, st>>>(ranges, (uint32_t)nb, w.tile_slices);
-    gsr_status s = gsr_scan_launch(w.tile_slices, nb, w.off, w.count, w.scan, st);
+    gsr_status s = list_slices(ranges, nb, w, st);
     if (s != GSR_OK) return s;
-    k_slice_emit<<<g, 256, 0, st>>>(w.tile_slices, w.off, (uint32_t)nb, w.cap, w.info);
     s = gsr_fill_u32_launch(counters, 0u, (int64_t)nb + 1, st);
     if (s != GSR_OK) return s;
     const SliceArgs sl{w.tile_slices, w.info, w.count, w.tprod, w.part, w.part2, w.cap, w.cap < 2048u ? w.cap : 2048u};
