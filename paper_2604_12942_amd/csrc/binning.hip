@@ -171,10 +171,8 @@ __global__ __launch_bounds__(256) void k_scan_write(const uint32_t *__restrict__
 // times over (kShortSort); 11M live keys take 12 (7 passes: 0.29 ms against 0.36 before).
 constexpr int kRadixItems = 12, kShortItems = 4;
 constexpr int64_t kShortSort = 1 << 22;  // live items are not known on the host: this is a capacity
-constexpr int kSelfScanBlocks = 64;      // up to here the scatter adds up the histogram rows by itself
 inline int radix_items(int64_t cap) { return cap <= kShortSort ? kShortItems : kRadixItems; }
 inline int64_t radix_blocks(int64_t cap) { return ceil_div(cap > 0 ? cap : 1, kSortThreads * radix_items(cap)); }
-// row stride of the histogram: whole 16-byte words
 inline int64_t radix_stride(int64_t cap) { return ceil_div(radix_blocks(cap), 4) * 4; }
 
 template <int ITEMS>
@@ -271,10 +269,8 @@ __global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ 
 // Block b sorts its tile: wave w owns a quarter of it, 64 items per round, so (wave, round, lane)
 // order is input order and each wave ranks its items with its own running digit counts, without a
 // workgroup barrier per round; the four waves' counts then give every digit's local start and each
-// wave's offset inside it.  SELF: the histogram rows hold plain counts (at most kSelfScanBlocks of
-// them) and every block adds up the blocks before it and all of them, so that a short sort needs no
-// row scan launch; otherwise the rows are scanned and totals given.
-template <int ITEMS, bool SELF>
+// wave's offset inside it.
+template <int ITEMS>
 __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                                                        uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
                                                        const uint32_t *__restrict__ vin2, uint32_t *__restrict__ vout2,
@@ -302,24 +298,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
         mv[r] = valid ? vin[idx] : 0u;
         mv2[r] = vin2 ? (valid ? vin2[idx] : 0u) : idx;
     }
-    uint32_t dtot = 0, before_blocks = 0;
-    if (SELF) {
-        const uint32_t live = (n + kTile - 1) / kTile;
-        const uint4 *row = reinterpret_cast<const uint4 *>(hist + t * stride);
-        for (uint32_t q = 0; 4 * q < live; q++) {
-            const uint4 x = row[q];
-            const uint32_t c[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-            for (uint32_t i = 0; i < 4; i++) {
-                const uint32_t v = 4 * q + i < live ? c[i] : 0u;
-                dtot += v;
-                before_blocks += 4 * q + i < blockIdx.x ? v : 0u;
-            }
-        }
-    } else {
-        dtot = totals[t];
-        before_blocks = hist[t * stride + blockIdx.x];
-    }
+    const uint32_t dtot = totals[t], before_blocks = hist[t * stride + blockIdx.x];
     for (int k = 0; k < 4; k++) s_wcnt[k][t] = 0;
     __syncthreads();
     const uint64_t lt = lanemask_lt();
@@ -677,11 +656,179 @@ __global__ __launch_bounds__(kSmallThreads) void k_tile_order_small(const uint32
     }
 }
 
+// ---- few keys: two launches per pass ------------------------------------------------------------
+// Each of the general path's three launches per pass costs its 3 to 5 us at some hundred thousand keys
+// whatever it does, and the host as much again where the launches are not captured.  Up to kFewSort
+// keys the live ones are cut into at most kFewRows chunks, few enough for every workgroup of the scatter
+// to add up the counts of all chunks itself (one row of 256 counts per chunk, read coalesced), and the
+// row scan goes.  (Counting the next digit in the scatter by atomics, one launch per pass, was slower:
+// atomics to one cache line follow each other in 26 ns, and a digit of few values has one line a chunk.)
+// A pass over 40k depth keys: 3.3 + 3.5 + 6.0 -> 2.6 + 6.8 us; a scan's two voxel sorts of 100k points,
+// with the rest of the initialisation, 156 -> 147 us.  Instances of 600k with two payloads break even
+// (3.7 + 4 + 8 -> 4 + 13 us), and 1.5M keys lose (22 -> 28 us): the line lies at 8 keys per thread.
+constexpr int kFewThreads = 1024, kFewRows = 128, kFewItems = 8;
+constexpr int64_t kFewSort = (int64_t)kFewThreads * kFewRows * kFewItems;
+
+// Keys per thread of n live keys; a chunk is kFewThreads times that.
+__device__ __forceinline__ uint32_t few_rounds(uint32_t n) {
+    return n ? (n + kFewThreads * kFewRows - 1) / (kFewThreads * kFewRows) : 1u;
+}
+
+// Digit counts of every chunk, one row each.
+__global__ __launch_bounds__(kFewThreads) void k_few_hist(const uint32_t *__restrict__ keys, const uint32_t *n_dev,
+                                                          uint32_t n_host, uint32_t cap, int shift,
+                                                          uint32_t *__restrict__ hist) {
+    __shared__ uint32_t s_cnt[4][kRadix];
+    const uint32_t n = dev_count(n_dev, n_host, cap), chunk = few_rounds(n) * kFewThreads;
+    const uint32_t base = blockIdx.x * chunk, t = threadIdx.x;
+    if (base >= n) return;
+    s_cnt[t >> kRadixBits][t & (kRadix - 1)] = 0u;
+    __syncthreads();
+    const uint32_t end = n - base < chunk ? n : base + chunk;
+    uint32_t *cnt = s_cnt[(t >> 6) & 3u];
+    for (uint32_t i = base + t; i < end; i += kFewThreads) {
+        const uint32_t d = (keys[i] >> shift) & (kRadix - 1);
+        // a wave of one digit (sorted input, high digits) adds once instead of 64 times to one word
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        const uint64_t same = __ballot(d == d0), on = __ballot(true);
+        if (same == on) {
+            if (__lane_id() == (int)__builtin_ctzll(on)) atomicAdd(&cnt[d0], (uint32_t)__popcll(on));
+        } else {
+            atomicAdd(&cnt[d], 1u);
+        }
+    }
+    __syncthreads();
+    if (t < kRadix) hist[blockIdx.x * kRadix + t] = s_cnt[0][t] + s_cnt[1][t] + s_cnt[2][t] + s_cnt[3][t];
+}
+
+// One pass: chunk b's keys go to their places, in input order within a digit.  Loads, ranks and LDS staging as in k_radix_scatter.
+template <int ITEMS>
+__global__ __launch_bounds__(kFewThreads) void k_few_pass(const uint32_t *__restrict__ kin,
+                                                          const uint32_t *__restrict__ vin,
+                                                          uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
+                                                          const uint32_t *__restrict__ vin2,
+                                                          uint32_t *__restrict__ vout2, const uint32_t *n_dev,
+                                                          uint32_t n_host, uint32_t cap, int shift,
+                                                          const uint32_t *__restrict__ hist) {
+    __shared__ __align__(16) uint32_t s_stage[kFewThreads * ITEMS > 32 * kRadix ? kFewThreads * ITEMS : 32 * kRadix];
+    __shared__ uint32_t s_cnt[16][kRadix];
+    __shared__ uint32_t s_gbase[kRadix];  // global minus local start of the digit
+    __shared__ uint32_t s_w[16];
+    const uint32_t n = dev_count(n_dev, n_host, cap), rounds = few_rounds(n), chunk = rounds * kFewThreads;
+    const uint32_t base = blockIdx.x * chunk;
+    if (base >= n) return;
+    const uint32_t t = threadIdx.x, w = t >> 6, lane = t & 63u;
+    const uint32_t first = base + w * rounds * 64 + lane;  // this thread's keys: first + 64 r
+    uint32_t mk[ITEMS], mv[ITEMS], mv2[ITEMS], pos[ITEMS];
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; r++) {
+        if (r >= rounds) continue;
+        const uint32_t i = first + r * 64;
+        mk[r] = i < n ? kin[i] : 0u;
+        mv[r] = i < n ? vin[i] : 0u;
+        mv2[r] = vin2 ? (i < n ? vin2[i] : 0u) : i;
+    }
+    // wave w adds up the counts of chunks w, w + 16, ...: all of them, and those before this one
+    const uint32_t rows = (n + chunk - 1) / chunk;
+    {
+        uint4 tot = make_uint4(0, 0, 0, 0), before = tot;
+#pragma unroll
+        for (uint32_t k = 0; k < kFewRows / 16; k++) {
+            const uint32_t row = k * 16 + w;
+            const uint4 c = row < rows ? reinterpret_cast<const uint4 *>(hist + row * kRadix)[lane] : make_uint4(0, 0, 0, 0);
+            const uint32_t m = row < blockIdx.x ? 0xffffffffu : 0u;
+            tot.x += c.x, tot.y += c.y, tot.z += c.z, tot.w += c.w;
+            before.x += c.x & m, before.y += c.y & m, before.z += c.z & m, before.w += c.w & m;
+        }
+        reinterpret_cast<uint4 *>(s_stage)[t] = tot;
+        reinterpret_cast<uint4 *>(s_stage)[kFewThreads + t] = before;
+    }
+    for (uint32_t q = t; q < 16 * kRadix; q += kFewThreads) s_cnt[q >> kRadixBits][q & (kRadix - 1)] = 0u;
+    __syncthreads();
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; r++) {
+        if (r >= rounds) continue;
+        const bool valid = first + r * 64 < n;
+        const uint32_t d = (mk[r] >> shift) & (kRadix - 1);
+        const uint64_t peers = match_digit8(d, valid);
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t seen = s_cnt[w][d];
+        pos[r] = seen + rank;
+        if (valid && rank == 0) s_cnt[w][d] = seen + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t c[16], sum = 0, dtot = 0, before = 0, all;
+    if (t < kRadix) {
+#pragma unroll
+        for (uint32_t k = 0; k < 16; k++) sum += c[k] = s_cnt[k][t];
+#pragma unroll
+        for (uint32_t k = 0; k < 16; k++) {
+            dtot += s_stage[k * kRadix + t];
+            before += s_stage[(16 + k) * kRadix + t];
+        }
+    }
+    uint32_t run = block_excl_scan1024(sum, s_w, &all);
+    const uint32_t gstart = block_excl_scan1024(dtot, s_w, &all) + before;
+    if (t < kRadix) {
+        s_gbase[t] = gstart - run;
+#pragma unroll
+        for (uint32_t k = 0; k < 16; k++) {
+            s_cnt[k][t] = run;
+            run += c[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; r++) {
+        if (r >= rounds) continue;
+        pos[r] += s_cnt[w][(mk[r] >> shift) & (kRadix - 1)];
+        if (first + r * 64 < n) s_stage[pos[r]] = mk[r];
+    }
+    __syncthreads();
+    const uint32_t bn = n - base < chunk ? n - base : chunk;
+    uint32_t dst[ITEMS];
+#pragma unroll
+    for (uint32_t r = 0; r < ITEMS; r++) {
+        if (r >= rounds) continue;
+        const uint32_t p = r * kFewThreads + t;
+        if (p < bn) {
+            const uint32_t k = s_stage[p];
+            dst[r] = s_gbase[(k >> shift) & (kRadix - 1)] + p;
+            kout[dst[r]] = k;
+        }
+    }
+    // the payloads take the same permutation through the same staging
+    const auto move = [&](const uint32_t *x, uint32_t *out) {
+        __syncthreads();
+#pragma unroll
+        for (uint32_t r = 0; r < ITEMS; r++) {
+            if (r >= rounds) continue;
+            if (first + r * 64 < n) s_stage[pos[r]] = x[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t r = 0; r < ITEMS; r++) {
+            if (r >= rounds) continue;
+            if (r * kFewThreads + t < bn) out[dst[r]] = s_stage[r * kFewThreads + t];
+        }
+    };
+    move(mv, vout);
+    if (vout2) move(mv2, vout2);
+}
+
 }  // namespace gsr
 
 using namespace gsr;
 
 namespace {
+
+// rows and words of the histogram of a sort of up to cap keys
+int64_t few_rows(int64_t cap) { return ceil_div(cap, kFewThreads) < kFewRows ? ceil_div(cap, kFewThreads) : kFewRows; }
+int64_t hist_words(int64_t cap) {
+    cap = cap > 0 ? cap : 1;
+    return kRadix * (cap <= kFewSort ? few_rows(cap) : radix_stride(cap));
+}
 
 struct BinWs {
     uint32_t *zk0, *zv0, *zk1, *zv1;  // depth sort ping-pong [VN]
@@ -689,7 +836,7 @@ struct BinWs {
     uint32_t *n_vis;                  // 1
     uint32_t *ik0, *ik1, *iv1, *iw1;  // instance sort [cap]
     uint32_t *tk0, *tk1, *tv1;        // tile-order sort [VT]
-    uint32_t *hist;                   // [256][max nb]
+    uint32_t *hist;                   // hist_words of the largest sort
     uint32_t *totals;                 // [256]
     size_t bytes;
 };
@@ -699,11 +846,10 @@ size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 BinWs layout(void *base, int64_t VN, int64_t cap, int64_t VT) {
     BinWs w{};
     const int64_t nb_vn = ceil_div(VN > 0 ? VN : 1, kSortTile);
-    // histogram rows are as long as the largest sort's block count
-    int64_t nbm = radix_stride(VN), nbc = radix_stride(cap);
-    nbm = nbm > nbc ? nbm : nbc;
-    nbc = radix_stride(VT);
-    nbm = nbm > nbc ? nbm : nbc;
+    // the largest sort's histogram
+    int64_t hw = hist_words(VN);
+    hw = hw > hist_words(cap) ? hw : hist_words(cap);
+    hw = hw > hist_words(VT) ? hw : hist_words(VT);
     char *p = static_cast<char *>(base);
     size_t off = 0;
     auto take = [&](size_t words) {
@@ -715,7 +861,7 @@ BinWs layout(void *base, int64_t VN, int64_t cap, int64_t VT) {
     w.vis_b = take(nb_vn); w.cnt_b = take(ceil_div(VN > 0 ? VN : 1, 256)); w.n_vis = take(1);
     w.ik0 = take(cap); w.ik1 = take(cap); w.iv1 = take(cap); w.iw1 = take(cap);
     w.tk0 = take(VT); w.tk1 = take(VT); w.tv1 = take(VT);
-    w.hist = take((size_t)kRadix * nbm); w.totals = take(kRadix);
+    w.hist = take((size_t)hw); w.totals = take(kRadix);
     w.bytes = off;
     return w;
 }
@@ -726,26 +872,25 @@ void radix_pass(const uint32_t *k, const uint32_t *v, uint32_t *k2, uint32_t *v2
                 hipStream_t st) {
     const int nb = (int)radix_blocks(cap), stride = (int)radix_stride(cap);
     k_radix_hist<ITEMS><<<nb, kSortThreads, 0, st>>>(k, n_dev, n_host, cap, shift, stride, hist);
-    if constexpr (ITEMS == kShortItems) {
-        if (nb <= kSelfScanBlocks) {
-            k_radix_scatter<ITEMS, true><<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, wout, n_dev, n_host, cap,
-                                                                      shift, stride, hist, totals);
-            return;
-        }
-    }
     k_radix_scan_rows<<<kRadix, 256, 0, st>>>(hist, nb, stride, kSortThreads * ITEMS, totals, n_dev, n_host, cap);
-    k_radix_scatter<ITEMS, false><<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, wout, n_dev, n_host, cap, shift,
-                                                               stride, hist, totals);
+    k_radix_scatter<ITEMS><<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, wout, n_dev, n_host, cap, shift, stride,
+                                                        hist, totals);
 }
 
 gsr_status radix_sort(uint32_t *&k, uint32_t *&v, uint32_t *&k2, uint32_t *&v2, const uint32_t *n_dev,
                       uint32_t n_host, uint32_t cap, int bits, uint32_t *hist, uint32_t *totals, hipStream_t st,
                       uint32_t **w = nullptr, uint32_t **w2 = nullptr, bool w_is_position = false) {
+    const bool few = cap <= kFewSort;
+    const int rows = (int)few_rows(cap);
     for (int shift = 0; shift < bits; shift += kRadixBits) {
         // w_is_position: the second payload starts as each item's input position, generated by
         // the first pass instead of read
         const uint32_t *win = w && !(w_is_position && shift == 0) ? *w : nullptr;
-        if (radix_items(cap) == kShortItems)
+        if (few) {
+            k_few_hist<<<rows, kFewThreads, 0, st>>>(k, n_dev, n_host, cap, shift, hist);
+            const auto pass = cap <= kFewThreads * kFewRows * 4 ? k_few_pass<4> : k_few_pass<kFewItems>;
+            pass<<<rows, kFewThreads, 0, st>>>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist);
+        } else if (radix_items(cap) == kShortItems)
             radix_pass<kShortItems>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist, totals, st);
         else
             radix_pass<kRadixItems>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist, totals, st);
@@ -878,7 +1023,7 @@ extern "C" gsr_status gsr_scan_launch(const uint32_t *in, int64_t n, uint32_t *o
 // ping-ponging between (k, v) and (k2, v2): the result is in (k, v) when ceil(bits / 8) is even,
 // else in (k2, v2).  ws: gsr_sort_pairs_ws_bytes(n).
 extern "C" size_t gsr_sort_pairs_ws_bytes(int64_t n) {
-    return (size_t)((int64_t)kRadix * radix_stride(n) * 4 + kRadix * 4 + 512);
+    return (size_t)(hist_words(n) * 4 + kRadix * 4 + 512);
 }
 
 // As gsr_sort_pairs_launch with the count read on the device (*n_dev, at most cap).
@@ -887,7 +1032,7 @@ extern "C" gsr_status gsr_sort_pairs_dev_launch(uint32_t *k, uint32_t *v, uint32
                                                 hipStream_t st) {
     if (cap == 0) return GSR_OK;
     uint32_t *hist = static_cast<uint32_t *>(ws);
-    uint32_t *totals = hist + (size_t)kRadix * radix_stride(cap);
+    uint32_t *totals = hist + (size_t)hist_words(cap);
     return radix_sort(k, v, k2, v2, n_dev, cap, cap, bits, hist, totals, st);
 }
 
@@ -895,7 +1040,7 @@ extern "C" gsr_status gsr_sort_pairs_launch(uint32_t *k, uint32_t *v, uint32_t *
                                             void *ws, hipStream_t st) {
     if (n == 0) return GSR_OK;
     uint32_t *hist = static_cast<uint32_t *>(ws);
-    uint32_t *totals = hist + (size_t)kRadix * radix_stride(n);
+    uint32_t *totals = hist + (size_t)hist_words(n);
     return radix_sort(k, v, k2, v2, nullptr, n, n, bits, hist, totals, st);
 }
 
@@ -906,7 +1051,7 @@ extern "C" gsr_status gsr_sort_positions_launch(uint32_t *k[2], uint32_t *v[2], 
                                                 void *ws, hipStream_t st) {
     if (n == 0) return GSR_OK;
     uint32_t *hist = static_cast<uint32_t *>(ws);
-    uint32_t *totals = hist + (size_t)kRadix * radix_stride(n);
+    uint32_t *totals = hist + (size_t)hist_words(n);
     return radix_sort(k[0], v[0], k[1], v[1], nullptr, n, n, bits, hist, totals, st, &w[0], &w[1], true);
 }
 

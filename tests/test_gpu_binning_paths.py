@@ -1,7 +1,8 @@
 """Binning at the edges of its paths, on drawn tile rectangles and depth keys with many ties, against
 numpy's lexicographic sort (integers: equal): one workgroup up to 8,192 pairs, block sums added up by
-their readers up to 524,288, histogram rows added up by the scatter up to 64 blocks, 4 or 12 keys per
-thread around a capacity of 4M, tile order in one workgroup up to 8,192 view-tiles, many view-tiles
+their readers up to 524,288, sorts of two launches per pass up to a capacity of 1M (1,024 keys a chunk up to
+131,072 live ones, whole and partial chunks, kernels for 4 and 8 times that), 4 or 12 keys per thread
+around a capacity of 4M, tile order in one workgroup up to 8,192 view-tiles, many view-tiles
 with few pairs, no visible pair, and an overflow."""
 import numpy as np
 import pytest
@@ -26,7 +27,10 @@ def _draw(rng, VN, raster, visible, wide):
     (1, 1, (64, 48), 100, 1.0, 2), (8192, 1, (320, 240), 1 << 16, 0.9, 3), (8193, 1, (320, 240), 1 << 16, 0.9, 3),
     (2731, 3, (333, 211), 65_537, 0.5, 4), (5000, 2, (160, 120), 1 << 15, 0.0, 3), (3000, 4, (4096, 2048), 1 << 16, 0.5, 3),
     (300_000, 1, (1280, 720), 1_200_000, 0.3, 5), (524_288, 1, (640, 360), (1 << 22), 0.2, 4),
-    (524_289, 1, (640, 360), (1 << 22) + 1, 0.2, 4), (175_000, 3, (1921, 1081), 1 << 20, 0.1, 5), (4000, 1, (320, 240), 5000, 1.0, 4)])
+    (524_289, 1, (640, 360), (1 << 22) + 1, 0.2, 4), (175_000, 3, (1921, 1081), 1 << 20, 0.1, 5), (4000, 1, (320, 240), 5000, 1.0, 4),
+    (131_072, 1, (640, 360), 1 << 17, 1.0, 1), (131_073, 1, (640, 360), 1 << 19, 1.0, 1),
+    (524_287, 1, (640, 360), (1 << 19) + 1, 1.0, 1), (130_000, 4, (640, 360), 1 << 20, 0.85, 2),
+    (150_000, 7, (640, 360), 1 << 20, 0.99, 1), (150_000, 7, (640, 360), (1 << 20) + 1, 0.99, 1)])
 def test_binning_paths_match_lexsort(n, V, size, cap, visible, wide):
     import paper_2604_12942_amd as gsr
     rng = np.random.default_rng(n + V + cap)
