@@ -68,7 +68,16 @@ __device__ __forceinline__ bool ellipse_meets_box(const float4 &A, const float4 
     return best <= B.y * 1.001f + 1e-3f;
 }
 
-// Pixel-centre box of the wave's 64 pixels in 32x32-block coordinates.
+// How a wave's 64 pixels lie in the tile.  The forward takes 8x8 boxes whatever the tile's shape: of all
+// the boxes of 64 pixels they are reached by the fewest ellipses, and a wave's pixels finish together.  Against
+// 16x4 (whole rows of a 16x16 tile): 583 -> 548 us at 4M Gaussians and 1920x1080, 346 -> 280 us on three
+// 640x360 views close to a wall, 76 -> 83 us on three far ones, whose tiles wait for their fullest box.
+// The backward takes whole rows of the tile (16x4 in a 16x16 tile): the split of a record's sum over the
+// waves, and with it the rounding of every gradient, is theirs.
+enum WaveShape : int { kBoxes = 0, kRows = 1 };
+constexpr int kBox = 8;
+
+// Pixel-centre box, in 32x32-block coordinates, of the 64 pixels of a wave of rows.
 template <int TW>
 __device__ __forceinline__ void wave_box(int tx0, int ty0, int w, float &x0, float &x1, float &y0, float &y1) {
     constexpr int rows = 64 / TW;
@@ -79,26 +88,36 @@ __device__ __forceinline__ void wave_box(int tx0, int ty0, int w, float &x0, flo
 }
 
 // ---- front-to-back walk -----------------------------------------------------------------------
-constexpr int kNullSlot = 256;    // LDS slot of the null Gaussian (cut-off below every exponent)
+// LDS slots of a batch: four groups of 64 staged Gaussians, each behind a null one (cut-off below every
+// exponent), so that index -1 of a group, which the bit search returns when none is left, is null.
+constexpr int kGroupSlots = 65, kSlots = 4 * kGroupSlots;
 constexpr float kGone = 1.0e30f;  // centre of a finished pixel: out of reach of every ellipse
 
 // The calling lane's pixel in one (view, tile) work item.
 struct TileGeom {
     int v, px, py;
+    int lp;  // row-major index of the pixel in its tile
     bool inside;
     double ox, oy;             // origin of the 32x32-aligned block holding the tile
     float fx, fy;              // pixel centre in block coordinates
     float wx0, wx1, wy0, wy1;  // the wave's box of pixel centres
 };
 
-template <int TW, int TH>
+template <int TW, int TH, int SHAPE>
 __device__ __forceinline__ TileGeom tile_geom(uint32_t item, int T, int ntx, int W, int H) {
+    static_assert(TW % kBox == 0 && TH % kBox == 0, "whole boxes");
     TileGeom t;
     t.v = item / T;
     const int tile = item % T;
     const int tx = tile % ntx, ty = tile / ntx;
-    t.px = tx * TW + (int)threadIdx.x % TW;
-    t.py = ty * TH + (int)threadIdx.x / TW;
+    const int w = (int)threadIdx.x >> 6, l = (int)threadIdx.x & 63;
+    // first column and row of the wave's box
+    const int bc = w % (TW / kBox) * kBox, br = w / (TW / kBox) * kBox;
+    const int lx = SHAPE == kRows ? (int)threadIdx.x % TW : bc + l % kBox;
+    const int ly = SHAPE == kRows ? (int)threadIdx.x / TW : br + l / kBox;
+    t.lp = ly * TW + lx;
+    t.px = tx * TW + lx;
+    t.py = ty * TH + ly;
     t.inside = t.px < W && t.py < H;
     // means are re-centred on the 32x32-aligned block holding the tile: the same origin for
     // every tile shape, so whole-tile images are bit-identical across 16x16, 8x32 and 32x8 tiles
@@ -107,13 +126,21 @@ __device__ __forceinline__ TileGeom tile_geom(uint32_t item, int T, int ntx, int
     t.oy = (double)by;
     t.fx = (float)(t.px - bx) + 0.5f;
     t.fy = (float)(t.py - by) + 0.5f;
-    wave_box<TW>(tx * TW - bx, ty * TH - by, (int)threadIdx.x >> 6, t.wx0, t.wx1, t.wy0, t.wy1);
+    if (SHAPE == kRows) {
+        wave_box<TW>(tx * TW - bx, ty * TH - by, w, t.wx0, t.wx1, t.wy0, t.wy1);
+    } else {
+        t.wx0 = (float)(tx * TW - bx + bc) + 0.5f;
+        t.wx1 = t.wx0 + (float)(kBox - 1);
+        t.wy0 = (float)(ty * TH - by + br) + 0.5f;
+        t.wy1 = t.wy0 + (float)(kBox - 1);
+    }
     return t;
 }
 
-// Per-pixel state of the walk.  A finished pixel (terminated, or outside the image) moves its
-// centre to kGone: the exponent then overflows to +inf, the pixel blends with weight 0, and the
-// loop needs no separate flag.
+// Per-pixel state of the walk.  A finished pixel (terminated, or outside the image) moves its centre to
+// kGone: the exponent then overflows to +inf, the pixel blends with weight 0, and the loop needs no
+// separate flag.  The transmittance of a live or finished pixel is at least GSR_T_MIN (a pixel that had
+// terminated before the walk keeps 1), so that a product below it says that a pixel terminates.
 struct PixelWalk {
     float Tr, c0, c1, c2, dd;
     uint32_t lst, nc;
@@ -122,20 +149,28 @@ struct PixelWalk {
 
 __device__ __forceinline__ PixelWalk walk_start(const TileGeom &t, float T0) {
     PixelWalk w;
-    w.Tr = T0;
+    const bool live = t.inside && T0 >= GSR_T_MIN;
+    w.Tr = live ? T0 : 1.0f;
     w.c0 = w.c1 = w.c2 = w.dd = 0.f;
     w.lst = w.nc = 0;
-    w.fxl = (t.inside && T0 >= GSR_T_MIN) ? t.fx : kGone;
+    w.fxl = live ? t.fx : kGone;
     return w;
 }
+
+// Index in the batch of the Gaussian whose slot lies at byte offset u.
+__device__ __forceinline__ uint32_t slot_index(uint32_t u) { return u / 16 - 1 - u / (16 * kGroupSlots); }
 
 // Composites the instances [lo, hi) of a tile list that begins at `start` (positions count from
 // it) into the walk.  The instances are staged through LDS in batches of 256; each wave tests
 // every staged ellipse against its pixel box and walks only the Gaussians that reach it, two per
-// step (the second one's LDS reads are in flight during the first blend; an odd last one is
-// paired with the null slot).  A wave stops at the first step after which all its pixels have
-// finished, the workgroup at the first batch none of its pixels needs.  Block-uniform arguments;
-// the null slot must have been written before the call.
+// step (an odd last one is paired with a null slot).  A wave stops at the first step after which all its pixels have
+// finished, the workgroup at the first batch none of its pixels needs.  Block-uniform arguments.
+// A long tile is walked by one wave per SIMD, which issues an instruction every 4 to 5 cycles, scalar ones
+// too: hence the bit search without selects, slot offsets kept in place of positions, and the whole of the
+// termination in a branch that few steps take (82 -> 62 instructions per pair of Gaussians).  With the boxes
+// above, the forward went from 588 to 468 us at 4M Gaussians and 1920x1080, from 762 to 668 us on the
+// corridor's eight 1280x720 views, from 341 to 226 us and from 74 to 70 us on three 640x360 views.  (Reading
+// the next pair or the next batch ahead changed nothing: the waits are not what bounds it.)
 // What a walk keeps besides the transmittance and the termination, from least to most: nothing
 // (the depth slices' transmittance products), the colour, depth and last contributor (an image),
 // also the number of contributors, or also (the second pass of the stored-contributor mode) the
@@ -148,6 +183,12 @@ __device__ __forceinline__ void composite(const gsr_splat *__restrict__ splats, 
                                           uint32_t start, uint32_t lo, uint32_t hi, const TileGeom &t,
                                           float4 *sA, float4 *sB, float4 *sC, PixelWalk &pw,
                                           uint32_t *__restrict__ clist, uint32_t cbase, uint32_t ccap) {
+    if (threadIdx.x < 4) {
+        sA[threadIdx.x * kGroupSlots] = make_float4(0.f, 0.f, 0.f, 0.f);
+        sB[threadIdx.x * kGroupSlots] = make_float4(0.f, -1.f, 0.f, 0.f);
+        sC[threadIdx.x * kGroupSlots] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    const int mine = threadIdx.x + threadIdx.x / 64 + 1;  // the slot this thread stages
     for (uint32_t b = lo; b < hi; b += 256) {
         if (__syncthreads_count(pw.fxl != kGone) == 0) break;
         const uint32_t e = b + threadIdx.x;
@@ -155,64 +196,86 @@ __device__ __forceinline__ void composite(const gsr_splat *__restrict__ splats, 
         if (e < hi) {
             float4 A, B, C;
             stage_splat(splats, inst[e], t.ox, t.oy, A, B, C);
-            sA[threadIdx.x] = A;
-            sB[threadIdx.x] = B;
-            sC[threadIdx.x] = C;
+            sA[mine] = A;
+            sB[mine] = B;
+            sC[mine] = C;
         }
         __syncthreads();
         const uint32_t pos0 = b - start + 1;
-        // one Gaussian's blend into this lane's pixel (branch-free: a non-contributing lane
-        // blends with weight exactly 0)
-        auto blend = [&](int j, const float4 &A, const float4 &B, const float4 &C) {
+        uint32_t lastu = 0;  // byte offset of the pixel's last composited slot of this batch, 0 if none
+        // one Gaussian's alpha at this lane's pixel (0 if it does not reach it)
+        auto alpha = [&](const float4 &A, const float4 &B, bool &reach) {
             float dx, dy, u1, u2;
             const float P = blend_exponent(A, B.x, pw.fxl, t.fy, dx, dy, u1, u2);
-            const bool cont = P <= B.y;
-            const float ar = B.z * __builtin_amdgcn_exp2f(-P);
-            const float a0 = cont ? fminf(ar, GSR_ALPHA_MAX) : 0.0f;
-            const float Tn = pw.Tr * (1.0f - a0);
-            const bool term = Tn < GSR_T_MIN;
-            pw.fxl = term ? kGone : pw.fxl;
-            const float a = term ? 0.0f : a0;
+            const float al = fminf(B.z * __builtin_amdgcn_exp2f(-P), GSR_ALPHA_MAX);
+            reach = P <= B.y;
+            return reach ? al : 0.0f;
+        };
+        // its blend into the pixel: weight a times the transmittance T in front of it
+        auto add = [&](uint32_t u, float a, float T, const float4 &B, const float4 &C) {
             if constexpr (KEEP >= kKeepImage) {
-                const float wgt = a * pw.Tr;
+                const float wgt = a * T;
                 pw.c0 = __builtin_fmaf(wgt, C.x, pw.c0);
                 pw.c1 = __builtin_fmaf(wgt, C.y, pw.c1);
                 pw.c2 = __builtin_fmaf(wgt, C.z, pw.c2);
                 pw.dd = __builtin_fmaf(wgt, B.w, pw.dd);
             }
-            pw.Tr = term ? pw.Tr : Tn;
-            if constexpr (KEEP >= kKeepImage) {
+            if constexpr (KEEP >= kKeepCount) {
                 const bool used = a > 0.0f;
-                if (KEEP == kKeepStore && used && cbase + pw.nc < ccap) clist[cbase + pw.nc] = pos0 - 1 + (uint32_t)j;
-                pw.lst = used ? pos0 + (uint32_t)j : pw.lst;
-                if constexpr (KEEP >= kKeepCount) pw.nc += used ? 1u : 0u;
+                if (KEEP == kKeepStore && used && cbase + pw.nc < ccap)
+                    clist[cbase + pw.nc] = pos0 - 1 + slot_index(u);
+                pw.nc += used ? 1u : 0u;
             }
         };
         for (int g = 0; g < 4 && g * 64 < cnt; g++) {
             if (__ballot(pw.fxl != kGone) == 0) break;
-            const int slot = g * 64 + __lane_id();
-            const bool r = slot < cnt && ellipse_meets_box(sA[slot], sB[slot], t.wx0, t.wx1, t.wy0, t.wy1);
+            const int first = g * kGroupSlots + 1, slot = first + __lane_id();
+            const bool r = g * 64 + __lane_id() < cnt && ellipse_meets_box(sA[slot], sB[slot], t.wx0, t.wx1, t.wy0, t.wy1);
             uint64_t m = __ballot(r);
+            uint32_t base;  // byte offset of the group's first slot, in a vector register
+            asm("v_mov_b32 %0, %1" : "=v"(base) : "s"(first * 16));
+            // byte offset of the next Gaussian's slot (the null one's behind the last)
+            auto next = [&]() {
+                int j;
+                asm("s_ff1_i32_b64 %0, %1" : "=s"(j) : "s"(m));
+                asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(j));
+                return ((uint32_t)j << 4) + base;
+            };
+            auto at = [](const float4 *x, uint32_t u) {
+                return *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(x) + u);
+            };
             while (m) {
-                const int j1 = g * 64 + __builtin_ctzll(m);
-                m &= m - 1;
-                const int j2 = m ? g * 64 + __builtin_ctzll(m) : kNullSlot;
-                m &= m - 1;
-                const float4 A1 = sA[j1], B1 = sB[j1], C1 = sC[j1];
-                const float4 A2 = sA[j2], B2 = sB[j2], C2 = sC[j2];
-                blend(j1, A1, B1, C1);
-                blend(j2, A2, B2, C2);
-                if (__ballot(pw.fxl != kGone) == 0) break;
+                const uint32_t u1 = next(), u2 = next();
+                const float4 A1 = at(sA, u1), B1 = at(sB, u1), C1 = at(sC, u1);
+                const float4 A2 = at(sA, u2), B2 = at(sB, u2), C2 = at(sC, u2);
+                __builtin_amdgcn_sched_barrier(0);  // all six reads in flight before the first blend
+                bool r1, r2;
+                float a1 = alpha(A1, B1, r1), a2 = alpha(A2, B2, r2);
+                uint32_t l = r1 ? u1 : lastu;
+                l = r2 ? u2 : l;
+                float T1 = pw.Tr * (1.0f - a1), T2 = T1 * (1.0f - a2);
+                if (__ballot(T2 < GSR_T_MIN)) {
+                    // a pixel terminates on one of the two, which is then not composited, nor anything after it
+                    const bool term1 = T1 < GSR_T_MIN;
+                    a1 = term1 ? 0.0f : a1;
+                    T1 = term1 ? pw.Tr : T1;
+                    a2 = term1 ? 0.0f : a2;
+                    T2 = T1 * (1.0f - a2);
+                    const bool term2 = T2 < GSR_T_MIN;
+                    a2 = term2 ? 0.0f : a2;
+                    T2 = term2 ? T1 : T2;
+                    l = a1 > 0.0f ? u1 : lastu;
+                    l = a2 > 0.0f ? u2 : l;
+                    pw.fxl = term1 || term2 ? kGone : pw.fxl;
+                    if (__ballot(pw.fxl != kGone) == 0) m = 0;
+                }
+                add(u1, a1, pw.Tr, B1, C1);
+                add(u2, a2, T1, B2, C2);
+                pw.Tr = T2;
+                lastu = l;
             }
         }
-    }
-}
-
-__device__ __forceinline__ void write_null_slot(float4 *sA, float4 *sB, float4 *sC) {
-    if (threadIdx.x == 0) {
-        sA[kNullSlot] = make_float4(0.f, 0.f, 0.f, 0.f);
-        sB[kNullSlot] = make_float4(0.f, -1.f, 0.f, 0.f);
-        sC[kNullSlot] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (KEEP >= kKeepImage && lastu) pw.lst = pos0 + slot_index(lastu);
     }
 }
 
@@ -241,7 +304,8 @@ struct SliceArgs {
     const uint32_t *tile_slices;  // [V*T] number of slices of each view-tile (0: whole tile)
     const uint2 *info;            // [cap] (view-tile, slice index within the tile)
     const uint32_t *count;        // [1] number of slices
-    float *tprod;                 // [cap][kSubs][256] per-pixel product of (1 - a) over each sub-slice
+    float *tprod;                 // [cap][kSubs][256] per pixel of the tile (row-major, as in the
+                                  // arrays below): product of (1 - a) over each sub-slice
     float4 *part;                 // [cap][256] slice colour (3) and depth, already times T_in
     uint2 *part2;                 // [cap][256] (T after the slice, negated if it terminated there;
                                   //             last composited position)
@@ -308,16 +372,16 @@ __global__ __launch_bounds__(1024) void k_slice_list(const uint32_t *__restrict_
 }
 
 // This pixel's product of (1 - a) over slice j, in sub-slice order.
-__device__ __forceinline__ float slice_prod(const SliceArgs &sl, uint32_t j) {
+__device__ __forceinline__ float slice_prod(const SliceArgs &sl, uint32_t j, int lp) {
     float P = 1.0f;
 #pragma unroll
-    for (uint32_t u = 0; u < kSubs; u++) P *= sl.tprod[((size_t)j * kSubs + u) * 256 + threadIdx.x];
+    for (uint32_t u = 0; u < kSubs; u++) P *= sl.tprod[((size_t)j * kSubs + u) * 256 + lp];
     return P;
 }
 
-__device__ __forceinline__ float slice_T_in(const SliceArgs &sl, uint32_t j, uint32_t k) {
+__device__ __forceinline__ float slice_T_in(const SliceArgs &sl, uint32_t j, uint32_t k, int lp) {
     float T = 1.0f;
-    for (uint32_t q = 0; q < k; q++) T *= slice_prod(sl, j - k + q);
+    for (uint32_t q = 0; q < k; q++) T *= slice_prod(sl, j - k + q, lp);
     return T;
 }
 
@@ -327,19 +391,18 @@ __global__ __launch_bounds__(256) void k_slice_prod(const gsr_splat *__restrict_
                                                     const uint32_t *__restrict__ inst,
                                                     const uint32_t *__restrict__ ranges, int W, int H, int ntx,
                                                     int T, SliceArgs sl) {
-    __shared__ float4 sA[257], sB[257], sC[257];
-    write_null_slot(sA, sB, sC);
+    __shared__ float4 sA[kSlots], sB[kSlots], sC[kSlots];
     const uint32_t n = min(*sl.count, sl.cap);
     for (uint64_t ju = blockIdx.x; ju < (uint64_t)n * kSubs; ju += gridDim.x) {
         const uint32_t j = (uint32_t)(ju / kSubs), u = (uint32_t)(ju % kSubs);
         const uint2 si = sl.info[j];
         if (si.x == kNoSlice || si.y + 1 == sl.tile_slices[si.x]) continue;
-        const TileGeom t = tile_geom<TW, TH>(si.x, T, ntx, W, H);
+        const TileGeom t = tile_geom<TW, TH, kBoxes>(si.x, T, ntx, W, H);
         const uint32_t start = ranges[2 * si.x], end = ranges[2 * si.x + 1];
         const uint32_t lo = min(start + si.y * kSliceLen + u * kSubLen, end), hi = min(lo + kSubLen, end);
         PixelWalk pw = walk_start(t, 1.0f);
         composite<kKeepTrans>(splats, inst, start, lo, hi, t, sA, sB, sC, pw, nullptr, 0u, 0u);
-        sl.tprod[(size_t)ju * 256 + threadIdx.x] = (t.inside && pw.fxl == kGone) ? 0.0f : pw.Tr;
+        sl.tprod[(size_t)ju * 256 + t.lp] = (t.inside && pw.fxl == kGone) ? 0.0f : pw.Tr;
     }
 }
 
@@ -358,7 +421,7 @@ __global__ __launch_bounds__(256) void k_slice_merge(const uint32_t *__restrict_
     for (uint32_t j = blockIdx.x; j < n; j += gridDim.x) {
         const uint2 si = sl.info[j];
         if (si.x == kNoSlice || si.y != 0) continue;
-        const TileGeom t = tile_geom<TW, TH>(si.x, T, ntx, W, H);
+        const TileGeom t = tile_geom<TW, TH, kBoxes>(si.x, T, ntx, W, H);
         if (!t.inside) continue;
         const uint32_t K = sl.tile_slices[si.x];
         float Tin = 1.0f, Tr = 1.0f, c0 = 0.f, c1 = 0.f, c2 = 0.f, dd = 0.f;
@@ -368,7 +431,7 @@ __global__ __launch_bounds__(256) void k_slice_merge(const uint32_t *__restrict_
                 kt = k - 1;
                 break;
             }
-            const size_t q = (size_t)(j + k) * 256 + threadIdx.x;
+            const size_t q = (size_t)(j + k) * 256 + t.lp;
             const float4 pc = sl.part[q];
             const uint2 p2 = sl.part2[q];
             c0 += pc.x;
@@ -382,12 +445,12 @@ __global__ __launch_bounds__(256) void k_slice_merge(const uint32_t *__restrict_
                 kt = k;
                 break;
             }
-            if (k + 1 < K) Tin *= slice_prod(sl, j + k);
+            if (k + 1 < K) Tin *= slice_prod(sl, j + k, t.lp);
         }
         {
             float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
             for (uint32_t k = K; k-- > 0;) {
-                const size_t q = (size_t)(j + k) * 256 + threadIdx.x;
+                const size_t q = (size_t)(j + k) * 256 + t.lp;
                 if (k > kt) {
                     sl.part[q] = acc;
                     sl.part2[q].x = __float_as_uint(Tr);
@@ -429,29 +492,28 @@ __global__ __launch_bounds__(256) void k_render_fwd(const gsr_splat *__restrict_
                                                     uint32_t *__restrict__ ncon, const uint32_t *__restrict__ coff,
                                                     uint32_t *__restrict__ clist, uint32_t ccap, SliceArgs sl) {
     static_assert(TW * TH == 256, "one pixel per lane");
-    __shared__ float4 sA[257], sB[257], sC[257];
-    write_null_slot(sA, sB, sC);
+    __shared__ float4 sA[kSlots], sB[kSlots], sC[kSlots];
     if (blockIdx.x < sl.grid) {
         const uint32_t n = min(*sl.count, sl.cap);
         for (uint32_t j = blockIdx.x; j < n; j += sl.grid) {
             const uint2 si = sl.info[j];
             if (si.x == kNoSlice) continue;
-            const TileGeom t = tile_geom<TW, TH>(si.x, T, ntx, W, H);
+            const TileGeom t = tile_geom<TW, TH, kBoxes>(si.x, T, ntx, W, H);
             const uint32_t start = ranges[2 * si.x], end = ranges[2 * si.x + 1];
             const uint32_t lo = start + si.y * kSliceLen, hi = min(lo + kSliceLen, end);
-            const float Tin = slice_T_in(sl, j, si.y);
+            const float Tin = slice_T_in(sl, j, si.y, t.lp);
             PixelWalk pw = walk_start(t, Tin);
             composite<kKeepImage>(splats, inst, start, lo, hi, t, sA, sB, sC, pw, nullptr, 0u, 0u);
             const bool term = t.inside && Tin >= GSR_T_MIN && pw.fxl == kGone;
-            sl.part[(size_t)j * 256 + threadIdx.x] = make_float4(pw.c0, pw.c1, pw.c2, pw.dd);
-            sl.part2[(size_t)j * 256 + threadIdx.x] = make_uint2(__float_as_uint(term ? -pw.Tr : pw.Tr), pw.lst);
+            sl.part[(size_t)j * 256 + t.lp] = make_float4(pw.c0, pw.c1, pw.c2, pw.dd);
+            sl.part2[(size_t)j * 256 + t.lp] = make_uint2(__float_as_uint(term ? -pw.Tr : pw.Tr), pw.lst);
         }
         return;
     }
     const uint32_t b = blockIdx.x - sl.grid, nb = gridDim.x - sl.grid;
     const uint32_t item = order ? order[b] : xcd_remap(b, nb);
     if (sl.grid && sl.tile_slices[item]) return;  // composited in slices
-    const TileGeom t = tile_geom<TW, TH>(item, T, ntx, W, H);
+    const TileGeom t = tile_geom<TW, TH, kBoxes>(item, T, ntx, W, H);
     const uint32_t start = ranges[2 * item], end = ranges[2 * item + 1];
     uint32_t cbase = 0;
     if (STORE && t.inside) cbase = coff[(int64_t)t.v * W * H + (int64_t)t.py * W + t.px];
@@ -571,9 +633,9 @@ __device__ __forceinline__ void group_incl_sum2(float &a, float &b, float ka, fl
     else row_incl_sum2(a, b, ka, kb);
 }
 
-// Shared memory of the backward of one tile (the staged splats keep the forward's null slot 256).
+// Shared memory of the backward of one tile (slots for the forward's batches, which the fused step walks in the same memory).
 struct BwdLds {
-    float4 sA[257], sB[257], sC[257];
+    float4 sA[kSlots], sB[kSlots], sC[kSlots];
     float sAcc[10][256];
     uint8_t sList[4][256];
     float4 sPG[4][64];    // dL/dC (3), dL/dD
@@ -923,7 +985,7 @@ __device__ __forceinline__ void slices_backward(const gsr_splat *__restrict__ sp
         const uint2 si = sl.info[j];
         if (si.x == kNoSlice) continue;
         __syncthreads();  // every lane has left the previous slice's shared state
-        const TileGeom t = tile_geom<TW, TH>(si.x, T, ntx, W, H);
+        const TileGeom t = tile_geom<TW, TH, kRows>(si.x, T, ntx, W, H);
         const int64_t pix = (int64_t)t.py * W + t.px;
         const gsr_camera &cam = cams[t.v];
         const uint32_t start = ranges[2 * si.x], len = ranges[2 * si.x + 1] - start;
@@ -933,7 +995,7 @@ __device__ __forceinline__ void slices_backward(const gsr_splat *__restrict__ sp
         if (t.inside) {
             grad(t, pix, pg);
             pg.last = last[(int64_t)t.v * P + pix];
-            const size_t q = (size_t)j * 256 + threadIdx.x;
+            const size_t q = (size_t)j * 256 + t.lp;
             const float4 cb = sl.part[q];  // colour and depth behind the slice
             PixelGrad fin = pg;
             fin.Tr = Tfin[(int64_t)t.v * P + pix];
@@ -965,7 +1027,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     const uint32_t bk = blockIdx.x - sl.grid, nb = gridDim.x - sl.grid;
     const uint32_t item = order ? order[bk] : xcd_remap(bk, nb);
     if (sl.grid && sl.tile_slices[item]) return;  // its backward runs in depth slices
-    const TileGeom t = tile_geom<TW, TH>(item, T, ntx, W, H);
+    const TileGeom t = tile_geom<TW, TH, kRows>(item, T, ntx, W, H);
     const int64_t pix = (int64_t)t.py * W + t.px;
     PixelGrad pg{1.f, 0.f, 0.f, 0.f, 0.f, 0u};
     if (t.inside) {
@@ -1061,7 +1123,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     __shared__ BwdLds L;
     __shared__ uint32_t s_item, s_flag;
     __shared__ double s_red[4];
-    write_null_slot(L.sA, L.sB, L.sC);
     const uint32_t n_sl = sl.grid ? min(*sl.count, sl.cap) : 0u;
     const uint32_t total = n_sl + VT;
     for (;;) {
@@ -1078,16 +1139,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
             const uint2 si = sl.info[it];
             if (si.x == kNoSlice) continue;
             item = si.x;
-            t = tile_geom<TW, TH>(item, T, ntx, W, H);
+            t = tile_geom<TW, TH, kRows>(item, T, ntx, W, H);
             start = ranges[2 * item];
             end = ranges[2 * item + 1];
             const uint32_t lo = start + si.y * kSliceLen, hi = min(lo + kSliceLen, end);
-            const float Tin = slice_T_in(sl, it, si.y);
+            const float Tin = slice_T_in(sl, it, si.y, t.lp);
             PixelWalk pw = walk_start(t, Tin);
             composite<kKeepImage>(splats, inst, start, lo, hi, t, L.sA, L.sB, L.sC, pw, nullptr, 0u, 0u);
             const bool term = t.inside && Tin >= GSR_T_MIN && pw.fxl == kGone;
-            sl.part[(size_t)it * 256 + threadIdx.x] = make_float4(pw.c0, pw.c1, pw.c2, pw.dd);
-            sl.part2[(size_t)it * 256 + threadIdx.x] = make_uint2(__float_as_uint(term ? -pw.Tr : pw.Tr), pw.lst);
+            sl.part[(size_t)it * 256 + t.lp] = make_float4(pw.c0, pw.c1, pw.c2, pw.dd);
+            sl.part2[(size_t)it * 256 + t.lp] = make_uint2(__float_as_uint(term ? -pw.Tr : pw.Tr), pw.lst);
             // release the slice's results, then count it; the workgroup that completes the tile's
             // last slice acquires every slice's results and finishes the tile
             __threadfence();
@@ -1106,7 +1167,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
             if (t.inside) {
                 for (uint32_t k = 0; k < K; k++) {
                     if (Tin2 < GSR_T_MIN) break;  // terminated in an earlier slice
-                    const size_t q = (size_t)(j0 + k) * 256 + threadIdx.x;
+                    const size_t q = (size_t)(j0 + k) * 256 + t.lp;
                     const float4 pc = sl.part[q];
                     const uint2 p2 = sl.part2[q];
                     c0 += pc.x;
@@ -1117,14 +1178,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                     Tr = fabsf(To);
                     lst = p2.y ? p2.y : lst;
                     if (To < 0.0f) break;  // terminated in this slice
-                    if (k + 1 < K) Tin2 *= slice_prod(sl, j0 + k);
+                    if (k + 1 < K) Tin2 *= slice_prod(sl, j0 + k, t.lp);
                 }
             }
             finish_pixels(t, item, cams[t.v], W, H, Tr, c0, c1, c2, dd, lst, rgb, depth, Tfin, last, a, pg, s_red);
         } else {
             item = order ? order[it - n_sl] : it - n_sl;
             if (sl.grid && sl.tile_slices[item]) continue;  // composited in slices
-            t = tile_geom<TW, TH>(item, T, ntx, W, H);
+            t = tile_geom<TW, TH, kRows>(item, T, ntx, W, H);
             start = ranges[2 * item];
             end = ranges[2 * item + 1];
             PixelWalk pw = walk_start(t, 1.0f);
@@ -1180,7 +1241,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     }
     const uint32_t bk = blockIdx.x - sl.grid, nb = gridDim.x - sl.grid;
     const uint32_t item = order ? order[bk] : xcd_remap(bk, nb);
-    const TileGeom t = tile_geom<TW, TH>(item, T, ntx, W, H);
+    const TileGeom t = tile_geom<TW, TH, kRows>(item, T, ntx, W, H);
     const int64_t pix = (int64_t)t.py * W + t.px;
     PixelGrad pg{1.f, 0.f, 0.f, 0.f, 0.f, 0u};
     double l = 0.0;
