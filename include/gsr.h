@@ -336,6 +336,13 @@ GSR_API gsr_status gsr_project_bwd(const gsr_gaussians *g, const gsr_camera *cam
                                    const gsr_emission *em, const uint32_t *tile_info, const gsr_param_grads *out,
                                    double *dpose, const int32_t *segment_id, int32_t min_segment, uint8_t *row_mask,
                                    void *ws, size_t ws_bytes, gsr_stream stream);
+/* As gsr_project_bwd, with the gradients STORED: every row of out is written, zero for Gaussians without
+ * one, so out need not be cleared. */
+GSR_API gsr_status gsr_project_bwd_set(const gsr_gaussians *g, const gsr_camera *cams, int32_t n_views,
+                                       const gsr_raster *r, const gsr_splat *splats, const float *dinst,
+                                       const gsr_emission *em, const uint32_t *tile_info, const gsr_param_grads *out,
+                                       double *dpose, const int32_t *segment_id, int32_t min_segment, uint8_t *row_mask,
+                                       void *ws, size_t ws_bytes, gsr_stream stream);
 
 /* ---- project backward fused with sparse Adam ---------------------------------------------------
  * The optimisation step's form of gsr_project_bwd followed by gsr_adam_step (Sec. III-C: visible

@@ -218,14 +218,15 @@ def project_bwd_workspace(n, n_views):
 
 
 def project_bwd(P, sh_degree, cams, n_views, raster, splats, dinst, em, tile_info, grads, dpose, ws,
-                segment_id=None, min_segment=0, row_mask=None):
+                segment_id=None, min_segment=0, row_mask=None, accumulate=True):
+    """Gradients are accumulated into grads; with accumulate=False they replace what grads hold."""
     g = _gauss_struct(P, sh_degree)
     gr = _abi.ParamGrads(*[grads[k].data_ptr() for k in PARAM_NAMES])
-    check(lib().gsr_project_bwd(C.byref(g), _ptr(cams), n_views, C.byref(raster.c), _ptr(splats), _ptr(dinst),
-                                _em(em), _ptr(tile_info), C.byref(gr), _ptr(dpose), _ptr(segment_id),
-                                int(min_segment), _ptr(row_mask), _ptr(ws),
-                                ws.numel() * ws.element_size() if ws is not None else 0, _stream()),
-          "gsr_project_bwd")
+    name = "gsr_project_bwd" if accumulate else "gsr_project_bwd_set"
+    check(getattr(lib(), name)(C.byref(g), _ptr(cams), n_views, C.byref(raster.c), _ptr(splats), _ptr(dinst),
+                               _em(em), _ptr(tile_info), C.byref(gr), _ptr(dpose), _ptr(segment_id),
+                               int(min_segment), _ptr(row_mask), _ptr(ws),
+                               ws.numel() * ws.element_size() if ws is not None else 0, _stream()), name)
 
 
 def visible_list_workspace(n):
@@ -667,13 +668,14 @@ class Rasterizer:
         return int(self.n_instances.item()) & 0xFFFFFFFF
 
     def backward(self, P, sh_degree, cams, dL_drgb, dL_ddepth, grads, want_pose=True, segment_id=None,
-                 min_segment=0, row_mask=None):
-        """render bwd -> project bwd; parameter gradients are accumulated into grads."""
+                 min_segment=0, row_mask=None, accumulate=True):
+        """render bwd -> project bwd; parameter gradients are accumulated into grads, or with accumulate=False
+        stored in them."""
         self.render_backward(cams, dL_drgb, dL_ddepth)
         if self.keep_dsplat:
             self.dsplat_copy = self.screen_grads()
         project_bwd(P, sh_degree, cams, self.V, self.raster, self.splats, self.dinst, self.em, self.tile_info, grads, self.dpose if want_pose else None, self.pose_ws, segment_id, min_segment,
-                    row_mask)
+                    row_mask, accumulate)
         return self.dpose
 
     def render_backward(self, cams, dL_drgb, dL_ddepth):
@@ -703,6 +705,7 @@ class _RasterizeFn(torch.autograd.Function):
         rgb, depth, Tf = rast.forward(P, sh_degree, cams)
         ctx.rast, ctx.sh_degree, ctx.cams = rast, sh_degree, cams
         ctx.P = P
+        ctx.set_materialize_grads(False)  # alpha's is never read, and a missing one of depth is zero below
         ctx.save_for_backward(means, log_scales, quats, opacity_logits, sh)
         alpha = 1.0 - Tf
         ctx.mark_non_differentiable(alpha)
@@ -712,11 +715,12 @@ class _RasterizeFn(torch.autograd.Function):
     def backward(ctx, g_rgb, g_depth, g_alpha):
         rast = ctx.rast
         P = ctx.P
-        grads = {k: torch.zeros_like(P[k]) for k in PARAM_NAMES}
+        grads = {k: torch.empty_like(P[k]) for k in PARAM_NAMES}
         if g_rgb is None:
             g_rgb = torch.zeros_like(rast.rgb)
-        dpose = rast.backward(P, ctx.sh_degree, ctx.cams, g_rgb, g_depth, grads, want_pose=True)
-        return (None, None, None, dpose.to(torch.float32).clone(), grads["means"], grads["log_scales"],
+        dpose = rast.backward(P, ctx.sh_degree, ctx.cams, g_rgb, g_depth, grads, want_pose=True,
+                              accumulate=False)
+        return (None, None, None, dpose.to(torch.float32), grads["means"], grads["log_scales"],
                 grads["quats"], grads["opacity_logits"], grads["sh"])
 
 

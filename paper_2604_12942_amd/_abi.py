@@ -99,6 +99,8 @@ _SIGS = {
     "gsr_project_bwd_workspace": ([C.c_int64, C.c_int32], C.c_size_t),
     "gsr_project_bwd": ([C.POINTER(Gaussians), P, C.c_int32, C.POINTER(Raster), P, P, C.POINTER(Emission), P,
                          C.POINTER(ParamGrads), P, P, C.c_int32, P, P, C.c_size_t, P], C.c_int),
+    "gsr_project_bwd_set": ([C.POINTER(Gaussians), P, C.c_int32, C.POINTER(Raster), P, P, C.POINTER(Emission), P,
+                         C.POINTER(ParamGrads), P, P, C.c_int32, P, P, C.c_size_t, P], C.c_int),
     "gsr_project_bwd_adam": ([C.POINTER(Gaussians), P, C.c_int32, C.POINTER(Raster), P, P, C.POINTER(Emission), P,
                               P, P, P, C.c_int32, C.POINTER(AdamFused), P, P, P, C.c_size_t, P], C.c_int),
     "gsr_visible_list_workspace": ([C.c_int64], C.c_size_t),

@@ -10,7 +10,7 @@ extern "C" gsr_status gsr_project_bwd_launch(const gsr_gaussians *, const gsr_ca
                                              const gsr_splat *, const float *, const gsr_emission *,
                                              const gsr_param_grads *, double *, const uint32_t *, const int32_t *,
                                              int32_t, uint8_t *, const gsr_adam_fused *, const uint32_t *,
-                                             const uint32_t *, void *, hipStream_t);
+                                             const uint32_t *, bool, void *, hipStream_t);
 extern "C" size_t gsr_visible_list_ws_bytes(int64_t n);
 extern "C" gsr_status gsr_visible_list_launch(const uint32_t *, int64_t, int, uint32_t *, uint32_t *, void *,
                                               hipStream_t);
@@ -332,11 +332,11 @@ extern "C" gsr_status gsr_pair_grads(const float *dinst, const gsr_emission *em,
     return gsr_pair_grads_launch(dinst, em, tile_info, (int64_t)n_views * n, dsplat, true, S(stream));
 }
 
-extern "C" gsr_status gsr_project_bwd(const gsr_gaussians *g, const gsr_camera *cams, int32_t n_views,
-                                      const gsr_raster *r, const gsr_splat *splats, const float *dinst,
-                                      const gsr_emission *em, const uint32_t *tile_info, const gsr_param_grads *out, double *dpose, const int32_t *segment_id,
-                                      int32_t min_segment, uint8_t *row_mask, void *ws, size_t ws_bytes,
-                                      gsr_stream stream) {
+static gsr_status project_bwd(const gsr_gaussians *g, const gsr_camera *cams, int32_t n_views, const gsr_raster *r,
+                              const gsr_splat *splats, const float *dinst, const gsr_emission *em,
+                              const uint32_t *tile_info, const gsr_param_grads *out, double *dpose,
+                              const int32_t *segment_id, int32_t min_segment, uint8_t *row_mask, bool set, void *ws,
+                              size_t ws_bytes, gsr_stream stream) {
     if (!gauss_ok(g) || !raster_ok(r) || n_views < 1 || !cams || !out) return GSR_E_INVALID;
     if ((int64_t)n_views * g->n >= (int64_t)UINT32_MAX) return GSR_E_INVALID;
     if (g->n > 0 && (!splats || !dinst || !emission_ok(em) || !tile_info || !out->means || !out->log_scales ||
@@ -345,7 +345,25 @@ extern "C" gsr_status gsr_project_bwd(const gsr_gaussians *g, const gsr_camera *
     if (g->n > 0 && (!ws || ws_bytes < gsr_project_bwd_workspace(g->n, n_views))) return GSR_E_CAPACITY;
     if ((reinterpret_cast<uintptr_t>(ws) & 255) != 0) return GSR_E_INVALID;
     return gsr_project_bwd_launch(g, cams, n_views, r, splats, dinst, em, out, dpose, tile_info, segment_id,
-                                  min_segment, row_mask, nullptr, nullptr, nullptr, ws, S(stream));
+                                  min_segment, row_mask, nullptr, nullptr, nullptr, set, ws, S(stream));
+}
+
+extern "C" gsr_status gsr_project_bwd(const gsr_gaussians *g, const gsr_camera *cams, int32_t n_views,
+                                      const gsr_raster *r, const gsr_splat *splats, const float *dinst,
+                                      const gsr_emission *em, const uint32_t *tile_info, const gsr_param_grads *out,
+                                      double *dpose, const int32_t *segment_id, int32_t min_segment, uint8_t *row_mask,
+                                      void *ws, size_t ws_bytes, gsr_stream stream) {
+    return project_bwd(g, cams, n_views, r, splats, dinst, em, tile_info, out, dpose, segment_id, min_segment, row_mask,
+                       false, ws, ws_bytes, stream);
+}
+
+extern "C" gsr_status gsr_project_bwd_set(const gsr_gaussians *g, const gsr_camera *cams, int32_t n_views,
+                                          const gsr_raster *r, const gsr_splat *splats, const float *dinst,
+                                          const gsr_emission *em, const uint32_t *tile_info, const gsr_param_grads *out,
+                                          double *dpose, const int32_t *segment_id, int32_t min_segment, uint8_t *row_mask,
+                                          void *ws, size_t ws_bytes, gsr_stream stream) {
+    return project_bwd(g, cams, n_views, r, splats, dinst, em, tile_info, out, dpose, segment_id, min_segment, row_mask,
+                       true, ws, ws_bytes, stream);
 }
 
 extern "C" gsr_status gsr_project_bwd_adam(const gsr_gaussians *g, const gsr_camera *cams, int32_t n_views,
@@ -368,7 +386,8 @@ extern "C" gsr_status gsr_project_bwd_adam(const gsr_gaussians *g, const gsr_cam
     if (g->n > 0 && (!ws || ws_bytes < gsr_project_bwd_workspace(g->n, n_views))) return GSR_E_CAPACITY;
     if ((reinterpret_cast<uintptr_t>(ws) & 255) != 0) return GSR_E_INVALID;
     return gsr_project_bwd_launch(g, cams, n_views, r, splats, dinst, em, nullptr, dpose, tile_info,
-                                  segment_id, min_segment, row_mask, adam, visible_list, visible_count, ws, S(stream));
+                                  segment_id, min_segment, row_mask, adam, visible_list, visible_count, false, ws,
+                                  S(stream));
 }
 
 extern "C" size_t gsr_visible_list_workspace(int64_t n) { return n < 0 ? 0 : gsr_visible_list_ws_bytes(n); }

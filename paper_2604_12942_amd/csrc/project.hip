@@ -375,11 +375,14 @@ struct FusedAdam {
 
 // Chain rule from the screen-space gradients (per pair, dsplat) to the parameters and the
 // per-view pose.  A Gaussian that no view rendered costs V 4-byte reads of tile_info and nothing
-// else.  FUSED:
-// instead of accumulating gradients, visible Gaussians of unfrozen segments take their sparse
-// Adam step directly from the register-held gradient (no gradient buffer round trip).  The SH
+// else.  What becomes of a Gaussian's gradient: kAdd accumulates it; kSet stores it, and zeros where no
+// view gives one, in whole lines (bound by HBM: 4M SH3 Gaussians of which a third is seen took 532 us
+// with reads of the old values after 140 us of clearing, and takes 376 us without either); kAdam, for visible Gaussians of
+// unfrozen segments, takes their sparse Adam step directly from the register-held gradient (no gradient
+// buffer round trip).  The SH
 // coefficient gradients accumulate across views in LDS ([coefficient][thread], conflict-free).
-template <int DEG, bool FUSED>
+enum GradMode : int { kAdd = 0, kSet = 1, kAdam = 2 };
+template <int DEG, int MODE>
 __global__ __launch_bounds__(256) void k_project_bwd(gsr_gaussians g, const gsr_camera *__restrict__ cams, int V,
                                                      int W, int H, const gsr_splat *__restrict__ splats,
                                                      const float *__restrict__ dsplat,
@@ -560,44 +563,53 @@ __global__ __launch_bounds__(256) void k_project_bwd(gsr_gaussians g, const gsr_
     }
     const bool unfrozen = !seg || (live && seg[i] >= min_seg);
     if (live && row_mask) row_mask[i] = (visible && unfrozen) ? 1 : 0;
-    if (!anyvis || !(touched || (FUSED && visible && unfrozen))) return;
-    // Sigma = M M^T, M = Rq diag(s): dL/dM = 2 dL/dSigma M
-    double qn[4], qnorm, Rq[3][3], sc[3];
-    unit_quat(qf, qn, qnorm);
-    quat_rot(qn[0], qn[1], qn[2], qn[3], Rq);
-    for (int a = 0; a < 3; a++) sc[a] = exp((double)lsf[a]);
-    double gRq[3][3];
-    float gls[3];
-    for (int c = 0; c < 3; c++) {
-        double gsc = 0;
+    const bool some = anyvis && (touched || (MODE == kAdam && visible && unfrozen));
+    if (!some && !(MODE == kSet && live)) return;
+    float gls[3] = {0.f, 0.f, 0.f}, gqf[4] = {0.f, 0.f, 0.f, 0.f}, gomf = 0.f;
+    if (some) {
+        // Sigma = M M^T, M = Rq diag(s): dL/dM = 2 dL/dSigma M
+        double qn[4], qnorm, Rq[3][3], sc[3];
+        unit_quat(qf, qn, qnorm);
+        quat_rot(qn[0], qn[1], qn[2], qn[3], Rq);
+        for (int a = 0; a < 3; a++) sc[a] = exp((double)lsf[a]);
+        double gRq[3][3];
+        for (int c = 0; c < 3; c++) {
+            double gsc = 0;
+            for (int a = 0; a < 3; a++) {
+                const double gm = 2.0 * (sym_at(gSig, a, 0) * Rq[0][c] + sym_at(gSig, a, 1) * Rq[1][c] +
+                                         sym_at(gSig, a, 2) * Rq[2][c]) * sc[c];
+                gsc += gm * Rq[a][c];
+                gRq[a][c] = gm * sc[c];
+            }
+            gls[c] = (float)(gsc * sc[c]);
+        }
+        // R(q) = (w^2 - |v|^2) I + 2 v v^T + 2 w [v]_x on the unit sphere
+        const double w = qn[0], vx = qn[1], vy = qn[2], vz = qn[3];
+        const double tr = gRq[0][0] + gRq[1][1] + gRq[2][2];
+        const double ax[3] = {gRq[2][1] - gRq[1][2], gRq[0][2] - gRq[2][0], gRq[1][0] - gRq[0][1]};
+        const double vv[3] = {vx, vy, vz};
+        double gq[4];
+        gq[0] = 2.0 * w * tr + 2.0 * (vx * ax[0] + vy * ax[1] + vz * ax[2]);
         for (int a = 0; a < 3; a++) {
-            const double gm = 2.0 * (sym_at(gSig, a, 0) * Rq[0][c] + sym_at(gSig, a, 1) * Rq[1][c] +
-                                     sym_at(gSig, a, 2) * Rq[2][c]) * sc[c];
-            gsc += gm * Rq[a][c];
-            gRq[a][c] = gm * sc[c];
+            double Gv = 0, GTv = 0;
+            for (int b = 0; b < 3; b++) {
+                Gv += gRq[a][b] * vv[b];
+                GTv += gRq[b][a] * vv[b];
+            }
+            gq[1 + a] = -2.0 * vv[a] * tr + 2.0 * (Gv + GTv) + 2.0 * w * ax[a];
         }
-        gls[c] = (float)(gsc * sc[c]);
+        const double qd = qn[0] * gq[0] + qn[1] * gq[1] + qn[2] * gq[2] + qn[3] * gq[3];
+        for (int a = 0; a < 4; a++) gqf[a] = (float)((gq[a] - qn[a] * qd) / qnorm);
+        gomf = (float)(gop * o * (1.0 - o));
     }
-    // R(q) = (w^2 - |v|^2) I + 2 v v^T + 2 w [v]_x on the unit sphere
-    const double w = qn[0], vx = qn[1], vy = qn[2], vz = qn[3];
-    const double tr = gRq[0][0] + gRq[1][1] + gRq[2][2];
-    const double ax[3] = {gRq[2][1] - gRq[1][2], gRq[0][2] - gRq[2][0], gRq[1][0] - gRq[0][1]};
-    const double vv[3] = {vx, vy, vz};
-    double gq[4];
-    gq[0] = 2.0 * w * tr + 2.0 * (vx * ax[0] + vy * ax[1] + vz * ax[2]);
-    for (int a = 0; a < 3; a++) {
-        double Gv = 0, GTv = 0;
-        for (int b = 0; b < 3; b++) {
-            Gv += gRq[a][b] * vv[b];
-            GTv += gRq[b][a] * vv[b];
-        }
-        gq[1 + a] = -2.0 * vv[a] * tr + 2.0 * (Gv + GTv) + 2.0 * w * ax[a];
-    }
-    const double qd = qn[0] * gq[0] + qn[1] * gq[1] + qn[2] * gq[2] + qn[3] * gq[3];
-    float gqf[4];
-    for (int a = 0; a < 4; a++) gqf[a] = (float)((gq[a] - qn[a] * qd) / qnorm);
-    const float gomf = (float)(gop * o * (1.0 - o));
-    if (!FUSED) {
+    if (MODE == kSet) {
+        for (int c = 0; c < 3; c++) out.log_scales[c * n + i] = gls[c];
+        for (int a = 0; a < 4; a++) out.quats[a * n + i] = gqf[a];
+        for (int a = 0; a < 3; a++) out.means[a * n + i] = (float)gmu[a];
+        out.opacity_logits[i] = gomf;
+#pragma unroll
+        for (int e = 0; e < 3 * K; e++) out.sh[e * n + i] = gh[e * 256];
+    } else if (MODE == kAdd) {
         for (int c = 0; c < 3; c++) out.log_scales[c * n + i] += gls[c];
         for (int a = 0; a < 4; a++) out.quats[a * n + i] += gqf[a];
         for (int a = 0; a < 3; a++) out.means[a * n + i] += (float)gmu[a];
@@ -759,7 +771,7 @@ extern "C" gsr_status gsr_project_bwd_launch(const gsr_gaussians *g, const gsr_c
                                              const gsr_emission *em, const gsr_param_grads *out,
                                              double *dpose, const uint32_t *tile_info, const int32_t *seg,
                                              int32_t min_seg, uint8_t *row_mask, const gsr_adam_fused *fa,
-                                             const uint32_t *vlist, const uint32_t *vcount, void *ws,
+                                             const uint32_t *vlist, const uint32_t *vcount, bool set, void *ws,
                                              hipStream_t st) {
     const int nb = (int)ceil_div(g->n, 256);
     if (nb == 0) {
@@ -796,9 +808,11 @@ extern "C" gsr_status gsr_project_bwd_launch(const gsr_gaussians *g, const gsr_c
         default: GSR_PB(3, F); break; \
     }
     if (fa) {
-        GSR_PBD(true)
+        GSR_PBD(kAdam)
+    } else if (set) {
+        GSR_PBD(kSet)
     } else {
-        GSR_PBD(false)
+        GSR_PBD(kAdd)
     }
 #undef GSR_PBD
 #undef GSR_PB
