@@ -129,13 +129,32 @@ __global__ __launch_bounds__(256) void k_vis_compact(const uint32_t *__restrict_
 }
 
 // ---- exclusive scan of a long uint32 array (the stored-contributor offsets) ------------------
+// The kSortItems consecutive words of one thread, in 16-byte accesses where they are whole and aligned (1.5M
+// words: the write took 12.5 us in single words, 5.5 us so).
+__device__ __forceinline__ bool whole_items(const uint32_t *p, int64_t base, int64_t n) {
+    return base + kSortItems <= n && (reinterpret_cast<uintptr_t>(p) & 15u) == 0;
+}
+__device__ __forceinline__ void load_items(const uint32_t *__restrict__ in, int64_t base, int64_t n,
+                                           uint32_t x[kSortItems]) {
+    if (whole_items(in, base, n)) {
+#pragma unroll
+        for (int k = 0; k < kSortItems / 4; k++) {
+            const uint4 q = reinterpret_cast<const uint4 *>(in + base)[k];
+            x[4 * k] = q.x, x[4 * k + 1] = q.y, x[4 * k + 2] = q.z, x[4 * k + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kSortItems; k++) x[k] = base + k < n ? in[base + k] : 0u;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_scan_sum(const uint32_t *__restrict__ in, int64_t n,
                                                   uint32_t *__restrict__ bsum) {
     __shared__ uint32_t s_w[4];
-    const int64_t base = (int64_t)blockIdx.x * kSortTile + threadIdx.x * kSortItems;
-    uint32_t c = 0;
+    uint32_t x[kSortItems], c = 0;
+    load_items(in, (int64_t)blockIdx.x * kSortTile + threadIdx.x * kSortItems, n, x);
 #pragma unroll
-    for (int k = 0; k < kSortItems; k++) c += base + k < n ? in[base + k] : 0u;
+    for (int k = 0; k < kSortItems; k++) c += x[k];
     uint32_t tot;
     block_excl_scan256(c, s_w, &tot);
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
@@ -146,16 +165,24 @@ __global__ __launch_bounds__(256) void k_scan_write(const uint32_t *__restrict__
     __shared__ uint32_t s_w[4];
     const int64_t base = (int64_t)blockIdx.x * kSortTile + threadIdx.x * kSortItems;
     uint32_t x[kSortItems], c = 0;
+    load_items(in, base, n, x);
 #pragma unroll
-    for (int k = 0; k < kSortItems; k++) {
-        x[k] = base + k < n ? in[base + k] : 0u;
-        c += x[k];
-    }
+    for (int k = 0; k < kSortItems; k++) c += x[k];
     uint32_t run = boff[blockIdx.x] + block_excl_scan256(c, s_w, nullptr);
 #pragma unroll
     for (int k = 0; k < kSortItems; k++) {
-        if (base + k < n) out[base + k] = run;
-        run += x[k];
+        const uint32_t v = x[k];
+        x[k] = run;
+        run += v;
+    }
+    if (whole_items(out, base, n)) {
+#pragma unroll
+        for (int k = 0; k < kSortItems / 4; k++)
+            reinterpret_cast<uint4 *>(out + base)[k] = make_uint4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kSortItems; k++)
+            if (base + k < n) out[base + k] = x[k];
     }
 }
 
