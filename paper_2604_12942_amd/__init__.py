@@ -402,10 +402,11 @@ def gicp_prepare(P, sh_degree, segment_id, src_segment, cams, n_cams, d_max, d_c
     n = G.n
     dev = P["means"].device
     if state is None or state["n"] != n:
+        # the statistics, the two set sizes and a registration's pose lie together: the host reads them at once
+        buf = torch.zeros(53, dtype=torch.float64, device=dev)
         state = dict(n=n, src_index=torch.empty(max(1, n), dtype=torch.int32, device=dev),
                      tgt_index=torch.empty(max(1, n), dtype=torch.int32, device=dev),
-                     counts=torch.zeros(2, dtype=torch.int32, device=dev),
-                     stats=torch.zeros(40, dtype=torch.float64, device=dev),
+                     counts=buf[40:41].view(torch.int32), stats=buf[:40], pose=buf[41:], buf=buf,
                      ws=torch.empty(max(1, lib().gsr_gicp_workspace(n)), dtype=torch.uint8, device=dev))
     state["d_corr"] = float(d_corr)
     check(lib().gsr_gicp_prepare(C.byref(G), _ptr(segment_id), src_segment, _ptr(cams), n_cams, d_max, d_corr,

@@ -3,7 +3,9 @@ map Gaussians seen from the views around a historical loopframe (Eq. 13-16), wit
 acceptance test, and propagation of a corrected pose to a segment of the map.
 
 Registration runs on the device end to end (set extraction, covariances, grid, Gauss-Newton with
-an on-device 6x6 solve); the host reads the statistics once, after the queued iterations.
+an on-device 6x6 solve).  The host queues 8 iterations, then as many again as it has queued so far, and
+reads the statistics after each batch: iterations after convergence do nothing, but their launches cost
+the host up to 18 us each (a registration that converged after 6 of 30: 776 -> 654 us).
 """
 from __future__ import annotations
 
@@ -24,17 +26,25 @@ def register(P, sh_degree, segment_id, src_segment, cams, n_cams, pose0=None, d_
     gsr_camera records).  pose0: (R [3, 3], t [3]) initial guess (identity by default).
     Returns a dict with R, t, converged, failed, iterations, count, cost, rmse, accepted, state."""
     dev = P["means"].device
-    state = gicp_prepare(P, sh_degree, segment_id, src_segment, cams, n_cams, d_max, d_corr, state)
     R0, t0 = (np.eye(3), np.zeros(3)) if pose0 is None else pose0
-    pose = torch.tensor(np.concatenate([np.asarray(R0, np.float64).ravel(), np.asarray(t0, np.float64)]),
-                        dtype=torch.float64, device=dev)
-    gicp_iterate(P, sh_degree, state, pose, max_iter)
-    st = state["stats"].cpu().numpy()
-    pz = pose.cpu().numpy()
+    start = torch.tensor(np.concatenate([np.asarray(R0, np.float64).ravel(), np.asarray(t0, np.float64)]),
+                         dtype=torch.float64, device=dev)
+    state = gicp_prepare(P, sh_degree, segment_id, src_segment, cams, n_cams, d_max, d_corr, state)
+    pose = state["pose"]
+    pose.copy_(start)
+    queued = 0
+    while True:
+        batch = min(queued or 8, max_iter - queued)
+        gicp_iterate(P, sh_degree, state, pose, batch)
+        queued += batch
+        host = state["buf"].cpu().numpy()
+        if host[36] or host[38] or queued >= max_iter:  # converged, failed
+            break
+    st, pz, sizes = host[:40], host[41:], host[40:41].view(np.int32)
     count = int(st[29])
     conv, failed = bool(st[36]), bool(st[38])
     cost = float(st[27])
     accepted = conv and not failed and count >= MIN_CORR and cost / count < ACCEPT_COST
     return dict(R=pz[:9].reshape(3, 3), t=pz[9:], converged=conv, failed=failed, iterations=int(st[37]),
                 count=count, cost=cost, rmse=float(np.sqrt(st[28] / max(count, 1))), accepted=accepted,
-                n_src=int(state["counts"][0].item()), n_tgt=int(state["counts"][1].item()), state=state)
+                n_src=int(sizes[0]), n_tgt=int(sizes[1]), state=state)
