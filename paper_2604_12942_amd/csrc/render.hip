@@ -540,97 +540,115 @@ __global__ __launch_bounds__(256) void k_render_fwd(const gsr_splat *__restrict_
 // row is masked off (row_mask) is not written and keeps its value, which is exactly the identity
 // step of the scan.  A VALU write of a register needs two wait states before a DPP read of it.
 // The whole wave must be active.
-// Two independent scans run interleaved: each DPP op's source was written two instructions
-// earlier (the other scan's op and an s_nop 0), which covers the same two wait states.  ka and
-// kb are values the caller derived from the inputs and needs afterwards: naming them as operands
-// makes them ready before the scan, so the scanned registers need no saved copies.
-// half_*: groups of 32 lanes (rows 0-1 and rows 2-3: the lane-15 broadcast is the last step);
-// row_*: groups of 16 lanes (each row on its own: the row shifts alone).
-__device__ __forceinline__ void half_incl_prod2(float &a, float &b, float ka, float kb) {
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf"
-        : "+v"(a), "+v"(b)
-        : "v"(ka), "v"(kb));
-}
-__device__ __forceinline__ void half_incl_sum2(float &a, float &b, float ka, float kb) {
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf"
-        : "+v"(a), "+v"(b)
-        : "v"(ka), "v"(kb));
-}
-__device__ __forceinline__ void row_incl_prod2(float &a, float &b, float ka, float kb) {
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_mul_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_mul_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(a), "+v"(b)
-        : "v"(ka), "v"(kb));
-}
-__device__ __forceinline__ void row_incl_sum2(float &a, float &b, float ka, float kb) {
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf"
-        : "+v"(a), "+v"(b)
-        : "v"(ka), "v"(kb));
+// Two independent scans run interleaved: each DPP op's source was written three instructions earlier
+// (the other scan's op and one of the backward's multiply-adds in between), which covers the two wait states
+// without idle slots: a wave alone on its SIMD, as in the longest tiles, waits for every slot.  Beside the
+// products (of 1 / (1 - a)) run the dot products g = dL/dC . c + dL/dD z of the two pixels, beside the
+// sums the colour and depth gradients cr..cd += dL/d. w, each in the order of its own additions.
+// ka and kb are values the caller derived from the inputs and needs afterwards: naming them as operands
+// makes them ready before the scan, so the scanned registers need no saved copies.  With idle slots in their
+// place, and the terms of a row formed again for every pixel pair in tiles wider than 8, k_render_bwd took 329
+// instead of 302 us on four 637x359 views, 69 instead of 63 on a 160x120 one and 1088 instead of 1053 at 4M
+// Gaussians and 1920x1080; the corridor's step, where other waves fill the slots, 1.90 ms as now.
+template <int GL>
+__device__ __forceinline__ void group_incl_prod2(float &a, float &b, float ka, float kb, float &g0, float &g1,
+                                                 const float4 &p0, const float4 &p1, const float4 &C, float z) {
+    static_assert(GL == 32 || GL == 16, "lane groups of 32 or 16");
+    if constexpr (GL == 32) {
+        asm volatile(
+            "v_mul_f32 %2, %7, %15\n\t"
+            "v_mul_f32 %3, %11, %15\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %6, %14\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %3, %10, %14\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %5, %13\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %3, %9, %13\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %4, %12\n\t"
+            "v_fmac_f32 %3, %8, %12"
+            : "+v"(a), "+v"(b), "=&v"(g0), "=&v"(g1)
+            : "v"(p0.x), "v"(p0.y), "v"(p0.z), "v"(p0.w), "v"(p1.x), "v"(p1.y), "v"(p1.z), "v"(p1.w), "v"(C.x),
+              "v"(C.y), "v"(C.z), "v"(z), "v"(ka), "v"(kb));
+    } else {
+        asm volatile(
+            "v_mul_f32 %2, %7, %15\n\t"
+            "v_mul_f32 %3, %11, %15\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %6, %14\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %3, %10, %14\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %5, %13\n\t"
+            "v_mul_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_mul_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %3, %9, %13\n\t"
+            "v_fmac_f32 %2, %4, %12\n\t"
+            "v_fmac_f32 %3, %8, %12"
+            : "+v"(a), "+v"(b), "=&v"(g0), "=&v"(g1)
+            : "v"(p0.x), "v"(p0.y), "v"(p0.z), "v"(p0.w), "v"(p1.x), "v"(p1.y), "v"(p1.z), "v"(p1.w), "v"(C.x),
+              "v"(C.y), "v"(C.z), "v"(z), "v"(ka), "v"(kb));
+    }
 }
 template <int GL>
-__device__ __forceinline__ void group_incl_prod2(float &a, float &b, float ka, float kb) {
+__device__ __forceinline__ void group_incl_sum2(float &a, float &b, float ka, float kb, float &cr, float &cg, float &cb,
+                                                float &cd, const float4 &p0, const float4 &p1, float w0, float w1) {
     static_assert(GL == 32 || GL == 16, "lane groups of 32 or 16");
-    if constexpr (GL == 32) half_incl_prod2(a, b, ka, kb);
-    else row_incl_prod2(a, b, ka, kb);
-}
-template <int GL>
-__device__ __forceinline__ void group_incl_sum2(float &a, float &b, float ka, float kb) {
-    static_assert(GL == 32 || GL == 16, "lane groups of 32 or 16");
-    if constexpr (GL == 32) half_incl_sum2(a, b, ka, kb);
-    else row_incl_sum2(a, b, ka, kb);
+    if constexpr (GL == 32) {
+        asm volatile(
+            "v_fmac_f32 %2, %10, %15\n\t"
+            "v_fmac_f32 %3, %11, %15\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %4, %12, %15\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %5, %13, %15\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %6, %14\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %3, %7, %14\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+            "v_fmac_f32 %4, %8, %14\n\t"
+            "v_fmac_f32 %5, %9, %14"
+            : "+v"(a), "+v"(b), "+v"(cr), "+v"(cg), "+v"(cb), "+v"(cd)
+            : "v"(p0.x), "v"(p0.y), "v"(p0.z), "v"(p0.w), "v"(p1.x), "v"(p1.y), "v"(p1.z), "v"(p1.w), "v"(w0), "v"(w1),
+              "v"(ka), "v"(kb));
+    } else {
+        asm volatile(
+            "v_fmac_f32 %2, %10, %15\n\t"
+            "v_fmac_f32 %3, %11, %15\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %4, %12, %15\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %5, %13, %15\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %2, %6, %14\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f32 %3, %7, %14\n\t"
+            "v_fmac_f32 %4, %8, %14\n\t"
+            "v_fmac_f32 %5, %9, %14"
+            : "+v"(a), "+v"(b), "+v"(cr), "+v"(cg), "+v"(cb), "+v"(cd)
+            : "v"(p0.x), "v"(p0.y), "v"(p0.z), "v"(p0.w), "v"(p1.x), "v"(p1.y), "v"(p1.z), "v"(p1.w), "v"(w0), "v"(w1),
+              "v"(ka), "v"(kb));
+    }
 }
 
 // Shared memory of the backward of one tile (slots for the forward's batches, which the fused step walks in the same memory).
@@ -805,28 +823,21 @@ __device__ __forceinline__ void tile_backward(const gsr_splat *__restrict__ spla
                 // up to each one (deepest first), which spares dividing by the product of (1 - a)
                 const float rom0 = __builtin_amdgcn_rcpf(om0), rom1 = __builtin_amdgcn_rcpf(om1);
                 float R0 = rom0, R1 = rom1;
-                group_incl_prod2<GL>(R0, R1, rom0, rom1);
+                float gs0, gs1;  // dL/dC . c + dL/dD z of the lane's Gaussian at the two pixels
+                group_incl_prod2<GL>(R0, R1, rom0, rom1, gs0, gs1, pg0, pg1, C, B.w);
                 // transmittance in front of each Gaussian: T behind the chunk times that product
                 // (at most 1e4, since T behind is at least T_final >= 1e-4)
                 const float Tb0 = T0 * R0;
                 const float Tb1 = T1 * R1;
                 const float w0 = a0 * Tb0, w1 = a1 * Tb1;
-                const float gs0 =
-                    __builtin_fmaf(pg0.x, C.x, __builtin_fmaf(pg0.y, C.y, __builtin_fmaf(pg0.z, C.z, pg0.w * B.w)));
-                const float gs1 =
-                    __builtin_fmaf(pg1.x, C.x, __builtin_fmaf(pg1.y, C.y, __builtin_fmaf(pg1.z, C.z, pg1.w * B.w)));
                 float in0 = w0 * gs0, in1 = w1 * gs1;
                 const float sb0 = S0 - in0, sb1 = S1 - in1;
-                group_incl_sum2<GL>(in0, in1, sb0, sb1);
+                // with it colour and depth: weight w = a T (zero for lanes that do not blend)
+                group_incl_sum2<GL>(in0, in1, sb0, sb1, cr, cg, cb, cd, pg0, pg1, w0, w1);
                 // everything behind each Gaussian
                 const float Sa0 = sb0 + in0, Sa1 = sb1 + in1;
                 const float d0 = __builtin_fmaf(Tb0, gs0, -Sa0 * rom0);
                 const float d1 = __builtin_fmaf(Tb1, gs1, -Sa1 * rom1);
-                // colour and depth: weight w = a T (zero for lanes that do not blend)
-                cr = __builtin_fmaf(pg0.x, w0, __builtin_fmaf(pg1.x, w1, cr));
-                cg = __builtin_fmaf(pg0.y, w0, __builtin_fmaf(pg1.y, w1, cg));
-                cb = __builtin_fmaf(pg0.z, w0, __builtin_fmaf(pg1.z, w1, cb));
-                cd = __builtin_fmaf(pg0.w, w0, __builtin_fmaf(pg1.w, w1, cd));
                 // unclamped alpha = o 2^-P: dL/do = 2^-P dL/da, dL/dP = -ln2 o (2^-P dL/da)
                 // (zero where the clamp holds alpha)
                 const bool lin0 = act0 && ar0 <= GSR_ALPHA_MAX, lin1 = act1 && ar1 <= GSR_ALPHA_MAX;
@@ -889,29 +900,29 @@ __device__ __forceinline__ void tile_backward(const gsr_splat *__restrict__ spla
                 mxy *= kz;
                 myy *= kz;
             } else {
-                for (int p = 0; p < 64; p += 2 * NG) {
-                    // this group's two pixels: 2 NG divides TW, so q0 and q1 sit in the row of p,
-                    // at columns p % TW + grp and + NG
-                    const int q0 = p + grp, q1 = p + NG + grp;
-                    const float fxp = fxw + (float)(p % TW);
-                    const float fx0 = fxp + (float)grp, fx1 = fxp + (float)(NG + grp);
-                    const float fy0 = fyw + (float)(p / TW);
-                    // the two pixels share a row, so dy and the terms of the exponent that depend
-                    // on dy alone are formed once
-                    const float dy = fy0 - A.y;
+                float fyr = fyw;
+                for (int r = 0; r < 64 / TW; r++, fyr += 1.0f) {
+                    // the pixels of a row share dy and the terms of the exponent that depend on dy alone
+                    const float dy = fyr - A.y;
                     const float l21dy = A.w * dy, u2 = B.x * dy, u22 = u2 * u2;
-                    const float dx0 = fx0 - A.x, dx1 = fx1 - A.x;
-                    float g0, g1;
-                    if (!pixel_pair(q0, q1, dx0, dx1, l21dy, u22, g0, g1)) continue;
-                    go += g0 + g1;
-                    const float dP0 = kz * g0, dP1 = kz * g1;
-                    mx = __builtin_fmaf(dP0, dx0, __builtin_fmaf(dP1, dx1, mx));
-                    const float sP = dP0 + dP1;
-                    my = __builtin_fmaf(sP, dy, my);
-                    const float qq0 = dP0 * dx0, qq1 = dP1 * dx1;
-                    mxx = __builtin_fmaf(qq0, dx0, __builtin_fmaf(qq1, dx1, mxx));
-                    mxy = __builtin_fmaf(qq0 + qq1, dy, mxy);
-                    myy = __builtin_fmaf(sP * dy, dy, myy);
+                    float fx0 = fxw + (float)grp;  // exact: pixel centres are small half-integers
+#pragma unroll 1
+                    for (int c = 0; c < TW; c += 2 * NG, fx0 += (float)(2 * NG)) {
+                        // this group's two pixels, at columns c + grp and + NG
+                        const int q0 = r * TW + c + grp, q1 = q0 + NG;
+                        const float dx0 = fx0 - A.x, dx1 = (fx0 + (float)NG) - A.x;
+                        float g0, g1;
+                        if (!pixel_pair(q0, q1, dx0, dx1, l21dy, u22, g0, g1)) continue;
+                        go += g0 + g1;
+                        const float dP0 = kz * g0, dP1 = kz * g1;
+                        mx = __builtin_fmaf(dP0, dx0, __builtin_fmaf(dP1, dx1, mx));
+                        const float sP = dP0 + dP1;
+                        my = __builtin_fmaf(sP, dy, my);
+                        const float qq0 = dP0 * dx0, qq1 = dP1 * dx1;
+                        mxx = __builtin_fmaf(qq0, dx0, __builtin_fmaf(qq1, dx1, mxx));
+                        mxy = __builtin_fmaf(qq0 + qq1, dy, mxy);
+                        myy = __builtin_fmaf(sP * dy, dy, myy);
+                    }
                 }
             }
             {
