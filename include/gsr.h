@@ -620,7 +620,10 @@ GSR_API gsr_status gsr_voxel_pca_cov(const float *points, const float *point_cov
  * beta = clamp(1 - rho, 0.5, 1), rho = the fraction of the segment's points that are reliable
  * but lack a valid prediction (segment [n] int32 in [0, n_segments), NULL = one segment).
  * pred may be NULL (no model).  Outputs: the parameter arrays of out ([c][n]) and branch [n]
- * (0 model, 1 PCA, 2 heuristic).  ws: gsr_cascade_workspace(n_segments) bytes. */
+ * (0 model, 1 PCA, 2 heuristic).  ws: gsr_cascade_workspace(n_segments) bytes.
+ * Of vox, point_voxel, reliable, s_pca and R are read, and n_voxels if it is not NULL: it tells how many
+ * voxels are worth preparing once for all their points, and no result depends on it.  out->sh serves as
+ * scratch memory until its values are written. */
 typedef struct {
     float *means, *log_scales, *quats, *opacity_logits, *sh;
 } gsr_params;

@@ -546,21 +546,25 @@ __device__ __forceinline__ uint8_t voxel_init(const gsr_voxels &V, const float *
 
 // Every voxel's VoxInit, computed once instead of once per point, in the sh output (written last, by
 // k_cascade_sh): records, then branch bytes.  There is room unless the voxels hold very few points
-// (sh holds 3 K floats per point); `table` decides on the device, where the voxel count is.  A point
+// (sh holds 3 K floats per point); `rows` decides on the device, where the voxel count is.  A point
 // then gathers one byte and one 32-byte record where it gathered some twenty values and formed a
 // quaternion in FP64: 6.4M points of 200k voxels in random order, 162 us and 34 for the table and the sh output (827 before), and
 // the segment counts 39 (228).
+// The count only says how many voxels the table holds: a point of a voxel past it takes the per-point form,
+// so the results do not depend on it.
 struct CascadeTable {
-    VoxInit *rec;  // null: no table (the sh output overlaps an input, or is not 16-byte aligned)
+    VoxInit *rec;  // null: no table (no count, or the sh output overlaps an input or is not 16-byte aligned)
     int64_t floats;  // of the sh output
-    __device__ __forceinline__ bool on(uint32_t nv) const { return rec && (int64_t)nv * 8 + (nv + 3) / 4 <= floats; }
+    __device__ __forceinline__ uint32_t rows(const gsr_voxels &V, int64_t n) const {
+        const uint32_t nv = rec ? *V.n_voxels : 0u;
+        return (int64_t)nv <= n && (int64_t)nv * 8 + (nv + 3) / 4 <= floats ? nv : 0u;
+    }
     __device__ __forceinline__ uint8_t *branch(uint32_t nv) const { return reinterpret_cast<uint8_t *>(rec + nv); }
 };
 
 __global__ __launch_bounds__(256) void k_cascade_voxels(gsr_voxels V, const float *__restrict__ pred, int64_t n,
                                                         int anchored, CascadeTable T) {
-    const uint32_t nv = *V.n_voxels;
-    if (!T.on(nv)) return;
+    const uint32_t nv = T.rows(V, n);
     for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < nv; v += gridDim.x * 256) {
         VoxInit o;
         const uint8_t br = voxel_init(V, pred, n, v, anchored, o);
@@ -586,13 +590,12 @@ __global__ __launch_bounds__(256) void k_seg_counts(const uint32_t *__restrict__
     if (lds)
         for (int e = threadIdx.x; e < nseg; e += 256) s_cnt[e] = s_fb[e] = 0u;
     __syncthreads();
-    const uint32_t nv = *V.n_voxels;
-    const bool table = T.on(nv);
+    const uint32_t nv = T.rows(V, n);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t v = pvox[i];
         const int s = seg ? seg[i] : 0;
         if (v == kOutside || s < 0 || s >= nseg) continue;
-        const bool f = table ? T.branch(nv)[v] == 1 : V.reliable[v] && !pred_valid(pred, n, v);
+        const bool f = v < nv ? T.branch(nv)[v] == 1 : V.reliable[v] && !pred_valid(pred, n, v);
         uint32_t *c = lds ? s_cnt : cnt, *b = lds ? s_fb : fb;
         const uint64_t here = __ballot(true), fall = __ballot(f);
         if (__ballot(s == __builtin_amdgcn_readfirstlane(s)) == here) {
@@ -623,16 +626,15 @@ __global__ void k_cascade(const float *__restrict__ pts, const float *__restrict
                           const float *__restrict__ pred, float focal, float beta_fixed,
                           const uint32_t *__restrict__ cnt, const uint32_t *__restrict__ fb, int K, CascadeTable T,
                           gsr_params out, uint8_t *__restrict__ branch, int anchored) {
-    const uint32_t nv = *V.n_voxels;
-    const bool table = T.on(nv);
+    const uint32_t nv = T.rows(V, n);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t v = V.point_voxel[i];
         for (int c = 0; c < 3; c++) out.means[c * n + i] = pts[c * n + i];
-        if (!table) write_sh(col, n, i, K, out.sh);
+        if (!nv) write_sh(col, n, i, K, out.sh);
         VoxInit o;
         uint8_t br = 2;
         if (v != kOutside) {
-            if (!table) {
+            if (v >= nv) {
                 br = voxel_init(V, pred, n, v, anchored, o);
             } else {
                 br = T.branch(nv)[v];
@@ -677,7 +679,7 @@ __global__ void k_cascade(const float *__restrict__ pts, const float *__restrict
 
 __global__ void k_cascade_sh(const float *__restrict__ col, int64_t n, gsr_voxels V, int K, CascadeTable T,
                              float *__restrict__ sh) {
-    if (!T.on(*V.n_voxels)) return;
+    if (!T.rows(V, n)) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         write_sh(col, n, i, K, sh);
 }
@@ -733,14 +735,14 @@ extern "C" gsr_status gsr_cascade_launch(const float *pts, const float *col, con
     if (s != GSR_OK) return s;
     const int g = grid(n), K = (sh_degree + 1) * (sh_degree + 1);
     // the sh output holds the voxel table until it is written, unless it shares memory with something
-    // read or written before that (a caller may convert colours in place)
+    // read or written before that (a caller may convert colours in place) or the caller gives no voxel count
     CascadeTable T{reinterpret_cast<VoxInit *>(out->sh), 3 * (int64_t)K * n};
     const uintptr_t lo = reinterpret_cast<uintptr_t>(out->sh), hi = lo + (uintptr_t)T.floats * 4;
     auto clash = [&](const void *p, int64_t bytes) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(p);
         return p && a < hi && a + (uintptr_t)bytes > lo;
     };
-    if ((lo & 15) || clash(pts, 12 * n) || clash(col, 12 * n) || clash(depth, 4 * n) || clash(seg, 4 * n) ||
+    if (!vox->n_voxels || (lo & 15) || clash(pts, 12 * n) || clash(col, 12 * n) || clash(depth, 4 * n) || clash(seg, 4 * n) ||
         clash(pred, 32 * n) || clash(vox->point_voxel, 4 * n) || clash(vox->reliable, n) || clash(vox->s_pca, 12 * n) ||
         clash(vox->R, 36 * n) || clash(vox->n_voxels, 4) || clash(out->means, 12 * n) || clash(out->log_scales, 12 * n) ||
         clash(out->quats, 16 * n) || clash(out->opacity_logits, 4 * n) || clash(branch, n) || clash(ws, gsr_cascade_ws_bytes(nseg)))
