@@ -747,6 +747,15 @@ extern "C" gsr_status gsr_cascade_launch(const float *pts, const float *col, con
         clash(vox->R, 36 * n) || clash(vox->n_voxels, 4) || clash(out->means, 12 * n) || clash(out->log_scales, 12 * n) ||
         clash(out->quats, 16 * n) || clash(out->opacity_logits, 4 * n) || clash(branch, n) || clash(ws, gsr_cascade_ws_bytes(nseg)))
         T.rec = nullptr;
+    // colours are read last, so with the table no other output may take their place before that
+    const uintptr_t c0 = reinterpret_cast<uintptr_t>(col), c1 = c0 + (uintptr_t)(12 * n);
+    auto over_colours = [&](const void *p, int64_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        return a < c1 && a + (uintptr_t)bytes > c0;
+    };
+    if (over_colours(out->means, 12 * n) || over_colours(out->log_scales, 12 * n) || over_colours(out->quats, 16 * n) ||
+        over_colours(out->opacity_logits, 4 * n) || over_colours(branch, n))
+        T.rec = nullptr;
     if (T.rec) k_cascade_voxels<<<g < 1024 ? g : 1024, 256, 0, st>>>(*vox, pred, n, anchored, T);
     k_seg_counts<<<g < 1024 ? g : 1024, 256, 0, st>>>(vox->point_voxel, *vox, pred, n, seg, nseg, T, cnt, fb);
     k_cascade<<<g, 256, 0, st>>>(pts, col, depth, seg, nseg, n, *vox, pred, focal, beta, cnt, fb, K, T, *out, branch,
