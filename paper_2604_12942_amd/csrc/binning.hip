@@ -850,11 +850,14 @@ using namespace gsr;
 
 namespace {
 
-// rows and words of the histogram of a sort of up to cap keys
+// rows and words of the histogram of a sort of up to cap keys; the words never shrink as cap grows (the long
+// sorts' blocks are larger, so theirs alone would): a workspace for more keys serves fewer, too
 int64_t few_rows(int64_t cap) { return ceil_div(cap, kFewThreads) < kFewRows ? ceil_div(cap, kFewThreads) : kFewRows; }
 int64_t hist_words(int64_t cap) {
     cap = cap > 0 ? cap : 1;
-    return kRadix * (cap <= kFewSort ? few_rows(cap) : radix_stride(cap));
+    if (cap <= kFewSort) return kRadix * few_rows(cap);
+    const int64_t most = cap > kShortSort ? radix_stride(kShortSort) : 0;
+    return kRadix * (radix_stride(cap) > most ? radix_stride(cap) : most);
 }
 
 struct BinWs {

@@ -405,7 +405,9 @@ VoxWs vox_layout(void *base, int64_t n) {
     w.rec = (float4 *)w.k[0];
     if (off < 8 * nb) take(8 * nb - off);
     w.sort_ws = take(gsr_sort_pairs_ws_bytes(n));
-    w.bsum = (uint32_t *)take((size_t)ceil_div(n > 0 ? n : 1, vox_tile(n)) * 4);
+    // (1,024 block sums at least above 2^20 points, where the blocks grow: the workspace never shrinks)
+    const int64_t blocks = ceil_div(n > 0 ? n : 1, vox_tile(n));
+    w.bsum = (uint32_t *)take((size_t)(n > (1 << 20) && blocks < 1024 ? 1024 : blocks) * 4);
     w.bytes = off;
     return w;
 }
