@@ -1056,12 +1056,17 @@ extern "C" size_t gsr_sort_pairs_ws_bytes(int64_t n) {
     return (size_t)(hist_words(n) * 4 + kRadix * 4 + 512);
 }
 
+// The histogram in a sort's workspace: k_few_pass reads its rows 16 bytes at a time (the 512 spare bytes leave room).
+static uint32_t *sort_hist(void *ws) {
+    return reinterpret_cast<uint32_t *>((reinterpret_cast<uintptr_t>(ws) + 15) & ~(uintptr_t)15);
+}
+
 // As gsr_sort_pairs_launch with the count read on the device (*n_dev, at most cap).
 extern "C" gsr_status gsr_sort_pairs_dev_launch(uint32_t *k, uint32_t *v, uint32_t *k2, uint32_t *v2,
                                                 const uint32_t *n_dev, uint32_t cap, int bits, void *ws,
                                                 hipStream_t st) {
     if (cap == 0) return GSR_OK;
-    uint32_t *hist = static_cast<uint32_t *>(ws);
+    uint32_t *hist = sort_hist(ws);
     uint32_t *totals = hist + (size_t)hist_words(cap);
     return radix_sort(k, v, k2, v2, n_dev, cap, cap, bits, hist, totals, st);
 }
@@ -1069,7 +1074,7 @@ extern "C" gsr_status gsr_sort_pairs_dev_launch(uint32_t *k, uint32_t *v, uint32
 extern "C" gsr_status gsr_sort_pairs_launch(uint32_t *k, uint32_t *v, uint32_t *k2, uint32_t *v2, uint32_t n, int bits,
                                             void *ws, hipStream_t st) {
     if (n == 0) return GSR_OK;
-    uint32_t *hist = static_cast<uint32_t *>(ws);
+    uint32_t *hist = sort_hist(ws);
     uint32_t *totals = hist + (size_t)hist_words(n);
     return radix_sort(k, v, k2, v2, nullptr, n, n, bits, hist, totals, st);
 }
@@ -1080,7 +1085,7 @@ extern "C" gsr_status gsr_sort_pairs_launch(uint32_t *k, uint32_t *v, uint32_t *
 extern "C" gsr_status gsr_sort_positions_launch(uint32_t *k[2], uint32_t *v[2], uint32_t *w[2], uint32_t n, int bits,
                                                 void *ws, hipStream_t st) {
     if (n == 0) return GSR_OK;
-    uint32_t *hist = static_cast<uint32_t *>(ws);
+    uint32_t *hist = sort_hist(ws);
     uint32_t *totals = hist + (size_t)hist_words(n);
     return radix_sort(k[0], v[0], k[1], v[1], nullptr, n, n, bits, hist, totals, st, &w[0], &w[1], true);
 }
