@@ -150,23 +150,26 @@ __global__ __launch_bounds__(256) void k_proximity(const float *__restrict__ map
                                                    double dd, const uint32_t *__restrict__ key,
                                                    const uint32_t *__restrict__ val, const uint32_t *__restrict__ bucket,
                                                    uint8_t *__restrict__ keep, uint32_t *__restrict__ flag) {
-    const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kProbeLanes;
+    constexpr int64_t kPer = 256 / kProbeLanes;  // new means of a workgroup at a time
     const int d = threadIdx.x % kProbeLanes;
-    bool found = false;
-    if (j < n_new && d < 27) {
-        const double px = nw[j], py = nw[n_new + j], pz = nw[2 * n_new + j];
-        const int64_t cx = cell_of(px, inv_cell), cy = cell_of(py, inv_cell), cz = cell_of(pz, inv_cell);
-        const uint32_t h = cell_hash(cx + d % 3 - 1, cy + (d / 3) % 3 - 1, cz + d / 9 - 1);
-        for (uint32_t e = grid_lower_bound(key, bucket, h); e < (uint32_t)n_map && key[e] == h && !found; e++) {
-            const uint32_t i = val[e];
-            // ((dx dx + dy dy) + dz dz) < d_min^2 in float64
-            found = sqdist_rn(px, py, pz, map[i], map[n_map + i], map[2 * n_map + i]) < dd;
+    for (int64_t j0 = blockIdx.x * kPer; j0 < n_new; j0 += gridDim.x * kPer) {
+        const int64_t j = j0 + threadIdx.x / kProbeLanes;
+        bool found = false;
+        if (j < n_new && d < 27) {
+            const double px = nw[j], py = nw[n_new + j], pz = nw[2 * n_new + j];
+            const int64_t cx = cell_of(px, inv_cell), cy = cell_of(py, inv_cell), cz = cell_of(pz, inv_cell);
+            const uint32_t h = cell_hash(cx + d % 3 - 1, cy + (d / 3) % 3 - 1, cz + d / 9 - 1);
+            for (uint32_t e = grid_lower_bound(key, bucket, h); e < (uint32_t)n_map && key[e] == h && !found; e++) {
+                const uint32_t i = val[e];
+                // ((dx dx + dy dy) + dz dz) < d_min^2 in float64
+                found = sqdist_rn(px, py, pz, map[i], map[n_map + i], map[2 * n_map + i]) < dd;
+            }
         }
-    }
-    const uint64_t any = __ballot(found) >> (__lane_id() & ~(kProbeLanes - 1)) & 0xffffffffull;
-    if (j < n_new && d == 0) {
-        keep[j] = any ? 0 : 1;
-        flag[j] = any ? 0u : 1u;
+        const uint64_t any = __ballot(found) >> (__lane_id() & ~(kProbeLanes - 1)) & 0xffffffffull;
+        if (j < n_new && d == 0) {
+            keep[j] = any ? 0 : 1;
+            flag[j] = any ? 0u : 1u;
+        }
     }
 }
 
@@ -416,7 +419,10 @@ extern "C" gsr_status gsr_proximity_launch(const float *map, int64_t n_map, cons
     gsr_status s = gsr_grid_build_launch(map, n_map, nullptr, nullptr, n_map, cell, w.k, w.v, w.k2, w.v2, w.bucket,
                                          w.sort, 0, st);
     if (s != GSR_OK) return s;
-    k_proximity<<<(unsigned)ceil_div(n_new, 256 / kProbeLanes), 256, 0, st>>>(map, n_map, nw, n_new, inv_cell, dd, w.k, w.v, w.bucket, keep, w.flag);
+    // (a launch takes fewer than 2^32 threads; a workgroup takes several sets of means beyond 2^20 of them)
+    const int64_t nb = ceil_div(n_new, 256 / kProbeLanes);
+    k_proximity<<<(unsigned)(nb < (1 << 20) ? nb : (1 << 20)), 256, 0, st>>>(map, n_map, nw, n_new, inv_cell, dd, w.k,
+                                                                            w.v, w.bucket, keep, w.flag);
     s = gsr_scan_launch(w.flag, n_new, w.off, n_keep, w.scan, st);
     if (s != GSR_OK) return s;
     k_compact_index<<<nblk(n_new), 256, 0, st>>>(w.flag, w.off, n_new, keep_index);
