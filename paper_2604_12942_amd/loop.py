@@ -20,6 +20,16 @@ D_CORR, D_MAX = 0.5, 30.0
 MIN_CORR, ACCEPT_COST = 100, 1.0
 
 
+def _lie_together(state):
+    """Whether the statistics, set sizes and pose of a state are parts of its one buffer, as gicp_prepare lays
+    them out.  In a copy of a state (cloned, moved or loaded tensor by tensor) they are not."""
+    if "buf" not in state or "pose" not in state:
+        return False
+    at = state["buf"].data_ptr()
+    return (state["stats"].data_ptr() == at and state["counts"].data_ptr() == at + 320 and
+            state["pose"].data_ptr() == at + 328)
+
+
 def register(P, sh_degree, segment_id, src_segment, cams, n_cams, pose0=None, d_max=D_MAX, d_corr=D_CORR,
              max_iter=30, state=None):
     """Aligns the Gaussians of segment src_segment to the target set seen from cams (device
@@ -30,14 +40,21 @@ def register(P, sh_degree, segment_id, src_segment, cams, n_cams, pose0=None, d_
     start = torch.tensor(np.concatenate([np.asarray(R0, np.float64).ravel(), np.asarray(t0, np.float64)]),
                          dtype=torch.float64, device=dev)
     state = gicp_prepare(P, sh_degree, segment_id, src_segment, cams, n_cams, d_max, d_corr, state)
-    pose = state["pose"]
-    pose.copy_(start)
+    together = _lie_together(state)
+    pose = start
+    if together:
+        pose = state["pose"]
+        pose.copy_(start)
     queued = 0
     while True:
         batch = min(queued or 8, max_iter - queued)
         gicp_iterate(P, sh_degree, state, pose, batch)
         queued += batch
-        host = state["buf"].cpu().numpy()
+        if together:
+            host = state["buf"].cpu().numpy()
+        else:
+            host = np.concatenate([state["stats"].cpu().numpy(), state["counts"].cpu().numpy().view(np.float64),
+                                   pose.cpu().numpy()])
         if host[36] or host[38] or queued >= max_iter:  # converged, failed
             break
     st, pz, sizes = host[:40], host[41:], host[40:41].view(np.int32)
