@@ -65,9 +65,18 @@ __global__ __launch_bounds__(256) void k_vox_heads(const uint32_t *__restrict__ 
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
+// A lane's 64-bit value, and the number of ones below the lowest zero.
+__device__ __forceinline__ uint64_t lane64(uint64_t x, int lane) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane) << 32;
+}
+__device__ __forceinline__ int ones_below(uint64_t m) { return ~m ? __builtin_ctzll(~m) : 64; }
+
+constexpr int kNear = 3;
+
 // Numbers the voxels, writes the points' order and voxels.  Points of one voxel whose leading hash bits
-// agree form a run that the sort left in index order: its first point writes the run in order of the
-// whole hash (distinct: SplitMix64 is a bijection).  bsum: the blocks' head counts, scanned when
+// agree form a run that the sort left in index order: each of them counts the run's smaller whole hashes
+// (distinct: SplitMix64 is a bijection), a lane alone within kNear points and its wave beyond.  bsum: the blocks' head counts, scanned when
 // `scanned`, else added up here (the last block then writes the voxel count).
 template <int ROUNDS>
 __global__ __launch_bounds__(256) void k_vox_assign(const uint32_t *__restrict__ skey, const uint32_t *__restrict__ sidx,
@@ -109,11 +118,10 @@ __global__ __launch_bounds__(256) void k_vox_assign(const uint32_t *__restrict__
         const uint32_t k = in ? skey[e] : 0u, p = in ? sidx[e] : 0u;
         const uint64_t out = __ballot(in && k == kOutside);
         if (out && lane == __builtin_ctzll(out)) atomicAdd(V.n_outside, (uint32_t)__popcll(out));
-        if (!in) continue;
         const bool head = (m[r] >> lane) & 1ull;
-        if (k == kOutside) {
+        if (in && k == kOutside) {
             V.point_voxel[p] = kOutside;
-        } else {
+        } else if (in) {
             const uint32_t v = b0 + s_cnt[r * 4 + w] + (uint32_t)__popcll(m[r] & lanemask_lt()) + (head ? 1u : 0u) - 1u;
             V.point_voxel[p] = v;
             if (head) {
@@ -121,21 +129,37 @@ __global__ __launch_bounds__(256) void k_vox_assign(const uint32_t *__restrict__
                 V.key[v] = k;
             }
         }
-        const uint64_t h = splitmix64(seed ^ (uint64_t)p) >> sh;
-        auto same = [&](int64_t q) { return skey[q] == k && splitmix64(seed ^ (uint64_t)sidx[q]) >> sh == h; };
-        if (e > 0 && same(e - 1)) continue;  // the run's first point writes it
-        int64_t end = e + 1;
-        while (end < n && same(end)) end++;
-        if (end == e + 1) {
-            V.point_order[e] = p;
-            continue;
-        }
-        for (int64_t a = e; a < end; a++) {
-            const uint32_t pa = sidx[a];
-            const uint64_t ha = splitmix64(seed ^ (uint64_t)pa);
-            int64_t rank = 0;
-            for (int64_t q = e; q < end; q++) rank += splitmix64(seed ^ (uint64_t)sidx[q]) < ha ? 1 : 0;
-            V.point_order[e + rank] = pa;
+        const uint64_t h = splitmix64(seed ^ (uint64_t)p);
+        auto hash = [&](int64_t q) { return splitmix64(seed ^ (uint64_t)sidx[q]); };
+        auto member = [&](int64_t q, uint32_t kr, uint64_t hr, uint64_t &hq) {  // of the run of key kr and leading bits hr
+            if (q < 0 || q >= n || skey[q] != kr) return false;
+            hq = hash(q);
+            return hq >> sh == hr;
+        };
+        // a lane walks a few points to either side by itself
+        uint64_t hq;
+        int64_t b = e - 1, f = e + 1, at = e;
+        for (; in && e - b <= kNear && member(b, k, h >> sh, hq); b--) at -= hq > h ? 1 : 0;
+        for (; in && f - e <= kNear && member(f, k, h >> sh, hq); f++) at += hq < h ? 1 : 0;
+        const bool run = in && (e - b > kNear || f - e > kNear);
+        if (in && !run) V.point_order[at] = p;
+        uint64_t left = __ballot(run);
+        while (left) {  // the run of the first lane left, by the whole wave
+            const int lead = __builtin_ctzll(left);
+            const uint32_t kr = (uint32_t)__builtin_amdgcn_readlane((int)k, lead);
+            const uint64_t hr = lane64(h, lead) >> sh;
+            int64_t lo = e - lane + lead, hi = lo + 1;
+            for (int c = 64; c == 64; lo -= c) c = ones_below(__ballot(member(lo - 1 - lane, kr, hr, hq)));
+            for (int c = 64; c == 64; hi += c) c = ones_below(__ballot(member(hi + lane, kr, hr, hq)));
+            uint32_t rank = 0;
+            for (int64_t q = lo; q < hi; q += 64) {
+                hq = q + lane < hi ? hash(q + lane) : 0u;
+                const int c = hi - q < 64 ? (int)(hi - q) : 64;
+                for (int i = 0; i < c; i++) rank += lane64(hq, i) < h ? 1u : 0u;
+            }
+            const bool mine = run && e >= lo && e < hi;
+            if (mine) V.point_order[lo + rank] = p;
+            left &= ~__ballot(mine);
         }
     }
 }
@@ -427,7 +451,8 @@ static gsr_status voxel_pca_run(const float *pts, int64_t n, uint64_t seed, cons
     // Leading hash bits sorted on: with 16, points of one voxel that agree in them are rare (1 in 130
     // voxels of 32 points holds two), and a run of them averages n / 2^16 points even if all points lie in
     // one voxel; beyond 2^24 points that bound asks for 24.  Two passes and the key's four instead of
-    // twelve (the whole hash, then the key).
+    // twelve (the whole hash, then the key).  All in one voxel, 4M and 16.7M points take 659 and 2,842 us (764 and
+    // 3,024 in twelve passes; 17,500 and 435,000 with one lane ordering a run).
     const int hash_bits = n <= (1 << 24) ? 16 : 24;
     k_vox_prep<<<g, 256, 0, st>>>(pts, n, seed, hash_bits, w.k[0], w.h[0], out->n_outside);
     gsr_status s = gsr_sort_positions_launch(w.h, w.k, w.i, (uint32_t)n, hash_bits, w.sort_ws, st);
