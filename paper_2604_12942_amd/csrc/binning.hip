@@ -192,25 +192,25 @@ __global__ __launch_bounds__(256) void k_scan_write(const uint32_t *__restrict__
 //
 // Long sorts take 12 keys per thread: a block's run of one digit is then 12 keys long on average, so
 // the scattered writes stay wide.  Short ones are bound by one block's latency (dependent loads, then
-// a chain of ITEMS rank rounds) on a chip they do not fill, and take 4: at 100k live keys the scatter
-// went from 13.1 to 5.4 us, at 600k with a second payload from 12.5 to 8, at 1.5M from 14.4 to 10.4 (the
-// histogram then from 5.0 to 6.3).  The line lies where 4 keys per thread have filled the chip sixteen
-// times over (kShortSort); 11M live keys take 12 (7 passes: 0.29 ms against 0.36 before).
+// a chain of ITEMS rank rounds) on a chip they do not fill, and take 4.  The choice follows the live
+// count, which only the device knows: a capacity says little (a registration sorts 240k targets of a map of
+// 1.5M rows: 14 us of its 632 less with 4).  The line is the largest sort that the two-launch form takes on
+// the host: four passes over 1.1M keys take 83 us either way, over 2M 121 with 4 and 109 with 12, over 4.1M
+// 224 and 187.
 constexpr int kRadixItems = 12, kShortItems = 4;
-constexpr int64_t kShortSort = 1 << 22;  // live items are not known on the host: this is a capacity
-inline int radix_items(int64_t cap) { return cap <= kShortSort ? kShortItems : kRadixItems; }
-inline int64_t radix_blocks(int64_t cap) { return ceil_div(cap > 0 ? cap : 1, kSortThreads * radix_items(cap)); }
-inline int64_t radix_stride(int64_t cap) { return ceil_div(radix_blocks(cap), 4) * 4; }
+constexpr uint32_t kShortSort = 1 << 20;  // live keys
+constexpr int kRadixTile = kSortThreads * kRadixItems, kShortTile = kSortThreads * kShortItems;
+inline int64_t radix_blocks(int64_t cap) {
+    const int64_t few = ceil_div(cap < (int64_t)kShortSort ? cap : (int64_t)kShortSort, kShortTile), all = ceil_div(cap, kRadixTile);
+    return all > few ? all : few;
+}
 
 template <int ITEMS>
-__global__ __launch_bounds__(256) void k_radix_hist(const uint32_t *__restrict__ keys, const uint32_t *n_dev,
-                                                    uint32_t n_host, uint32_t cap, int shift, int stride,
-                                                    uint32_t *__restrict__ hist) {
+__device__ __forceinline__ void radix_hist_block(const uint32_t *__restrict__ keys, uint32_t n, uint32_t cap, int shift,
+                                                 int nblocks, uint32_t *__restrict__ hist, uint32_t *cnt) {
     // Counts are order-free: each thread takes ITEMS consecutive keys (16-byte loads) and adds a run
     // of equal digits to the block's LDS count in one atomic, so nearly sorted input (long runs)
     // costs one add per run and shuffled input one per key.
-    __shared__ uint32_t cnt[kRadix];
-    const uint32_t n = dev_count(n_dev, n_host, cap);
     // blocks past the live count write nothing: the row scan and the scatter skip them
     if (blockIdx.x * (uint32_t)(kSortThreads * ITEMS) >= n) return;
     cnt[threadIdx.x] = 0;
@@ -244,20 +244,30 @@ __global__ __launch_bounds__(256) void k_radix_hist(const uint32_t *__restrict__
         atomicAdd(&cnt[d], run);
     }
     __syncthreads();
-    hist[threadIdx.x * stride + blockIdx.x] = cnt[threadIdx.x];
+    hist[threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];
+}
+
+__global__ __launch_bounds__(256) void k_radix_hist(const uint32_t *__restrict__ keys, const uint32_t *n_dev,
+                                                    uint32_t n_host, uint32_t cap, int shift, int nblocks,
+                                                    uint32_t *__restrict__ hist) {
+    __shared__ uint32_t cnt[kRadix];
+    const uint32_t n = dev_count(n_dev, n_host, cap);
+    if (n <= kShortSort) radix_hist_block<kShortItems>(keys, n, cap, shift, nblocks, hist, cnt);
+    else radix_hist_block<kRadixItems>(keys, n, cap, shift, nblocks, hist, cnt);
 }
 
 // Row d of hist (one row per digit, row stride nblocks) is scanned exclusively in place over the
 // blocks that hold live items; the row total goes to totals[d].
-__global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ hist, int nblocks, int stride,
-                                                         int tile, uint32_t *__restrict__ totals,
-                                                         const uint32_t *n_dev, uint32_t n_host, uint32_t cap) {
+__global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ hist, int nblocks,
+                                                         uint32_t *__restrict__ totals, const uint32_t *n_dev,
+                                                         uint32_t n_host, uint32_t cap) {
     // one digit's row per workgroup; each thread owns a contiguous run of the row: sum it, one
     // workgroup scan of the run sums, then rewrite the run as exclusive prefixes.  Runs of up to
     // 16 entries (up to 4096 live blocks) stay in registers, loaded all at once.
     __shared__ uint32_t s_w[4];
-    uint32_t *row = hist + (int64_t)blockIdx.x * stride;
+    uint32_t *row = hist + (int64_t)blockIdx.x * nblocks;
     const uint32_t n = dev_count(n_dev, n_host, cap);
+    const uint32_t tile = n <= kShortSort ? kShortTile : kRadixTile;
     const int live = (int)((n + tile - 1) / tile);
     const int nb = live < nblocks ? live : nblocks;
     const int per = (nb + 255) / 256;
@@ -298,19 +308,15 @@ __global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *__restrict__ 
 // workgroup barrier per round; the four waves' counts then give every digit's local start and each
 // wave's offset inside it.
 template <int ITEMS>
-__global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
-                                                       uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
-                                                       const uint32_t *__restrict__ vin2, uint32_t *__restrict__ vout2,
-                                                       const uint32_t *n_dev, uint32_t n_host, uint32_t cap, int shift,
-                                                       int stride, const uint32_t *__restrict__ hist,
-                                                       const uint32_t *__restrict__ totals) {
+__device__ __forceinline__ void radix_scatter_block(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
+                                                    uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
+                                                    const uint32_t *__restrict__ vin2, uint32_t *__restrict__ vout2,
+                                                    uint32_t n, int shift, int nblocks,
+                                                    const uint32_t *__restrict__ hist,
+                                                    const uint32_t *__restrict__ totals, uint32_t *s_keys,
+                                                    uint32_t *s_vals, uint32_t (*s_wcnt)[kRadix], uint32_t *s_gbase,
+                                                    uint32_t *s_w) {
     constexpr int kTile = kSortThreads * ITEMS, kWaveItems = kTile / 4;
-    __shared__ uint32_t s_keys[kTile];
-    __shared__ uint32_t s_vals[kTile];
-    __shared__ uint32_t s_wcnt[4][kRadix];  // per-wave running counts, then per-wave starts
-    __shared__ uint32_t s_gbase[kRadix];    // global minus local start of the digit
-    __shared__ uint32_t s_w[4];
-    const uint32_t n = dev_count(n_dev, n_host, cap);
     const uint32_t base = blockIdx.x * kTile;
     if (base >= n) return;
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
@@ -325,7 +331,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
         mv[r] = valid ? vin[idx] : 0u;
         mv2[r] = vin2 ? (valid ? vin2[idx] : 0u) : idx;
     }
-    const uint32_t dtot = totals[t], before_blocks = hist[t * stride + blockIdx.x];
+    const uint32_t dtot = totals[t], before_blocks = hist[t * nblocks + blockIdx.x];
     for (int k = 0; k < 4; k++) s_wcnt[k][t] = 0;
     __syncthreads();
     const uint64_t lt = lanemask_lt();
@@ -387,6 +393,26 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restric
             if (p < bn) vout2[dst[r]] = s_vals[p];
         }
     }
+}
+
+__global__ __launch_bounds__(256) void k_radix_scatter(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
+                                                       uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
+                                                       const uint32_t *__restrict__ vin2, uint32_t *__restrict__ vout2,
+                                                       const uint32_t *n_dev, uint32_t n_host, uint32_t cap, int shift,
+                                                       int nblocks, const uint32_t *__restrict__ hist,
+                                                       const uint32_t *__restrict__ totals) {
+    __shared__ uint32_t s_keys[kRadixTile];
+    __shared__ uint32_t s_vals[kRadixTile];
+    __shared__ uint32_t s_wcnt[4][kRadix];  // per-wave running counts, then per-wave starts
+    __shared__ uint32_t s_gbase[kRadix];    // global minus local start of the digit
+    __shared__ uint32_t s_w[4];
+    const uint32_t n = dev_count(n_dev, n_host, cap);
+    if (n <= kShortSort)
+        radix_scatter_block<kShortItems>(kin, vin, kout, vout, vin2, vout2, n, shift, nblocks, hist, totals, s_keys, s_vals,
+                                         s_wcnt, s_gbase, s_w);
+    else
+        radix_scatter_block<kRadixItems>(kin, vin, kout, vout, vin2, vout2, n, shift, nblocks, hist, totals, s_keys, s_vals,
+                                         s_wcnt, s_gbase, s_w);
 }
 
 // ---- instance emission in depth order --------------------------------------------------------
@@ -850,14 +876,11 @@ using namespace gsr;
 
 namespace {
 
-// rows and words of the histogram of a sort of up to cap keys; the words never shrink as cap grows (the long
-// sorts' blocks are larger, so theirs alone would): a workspace for more keys serves fewer, too
+// rows and words of the histogram of a sort of up to cap keys (never fewer words for more keys)
 int64_t few_rows(int64_t cap) { return ceil_div(cap, kFewThreads) < kFewRows ? ceil_div(cap, kFewThreads) : kFewRows; }
 int64_t hist_words(int64_t cap) {
     cap = cap > 0 ? cap : 1;
-    if (cap <= kFewSort) return kRadix * few_rows(cap);
-    const int64_t most = cap > kShortSort ? radix_stride(kShortSort) : 0;
-    return kRadix * (radix_stride(cap) > most ? radix_stride(cap) : most);
+    return kRadix * (cap <= kFewSort ? few_rows(cap) : radix_blocks(cap));
 }
 
 struct BinWs {
@@ -896,22 +919,11 @@ BinWs layout(void *base, int64_t VN, int64_t cap, int64_t VT) {
     return w;
 }
 
-template <int ITEMS>
-void radix_pass(const uint32_t *k, const uint32_t *v, uint32_t *k2, uint32_t *v2, const uint32_t *win, uint32_t *wout,
-                const uint32_t *n_dev, uint32_t n_host, uint32_t cap, int shift, uint32_t *hist, uint32_t *totals,
-                hipStream_t st) {
-    const int nb = (int)radix_blocks(cap), stride = (int)radix_stride(cap);
-    k_radix_hist<ITEMS><<<nb, kSortThreads, 0, st>>>(k, n_dev, n_host, cap, shift, stride, hist);
-    k_radix_scan_rows<<<kRadix, 256, 0, st>>>(hist, nb, stride, kSortThreads * ITEMS, totals, n_dev, n_host, cap);
-    k_radix_scatter<ITEMS><<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, wout, n_dev, n_host, cap, shift, stride,
-                                                        hist, totals);
-}
-
 gsr_status radix_sort(uint32_t *&k, uint32_t *&v, uint32_t *&k2, uint32_t *&v2, const uint32_t *n_dev,
                       uint32_t n_host, uint32_t cap, int bits, uint32_t *hist, uint32_t *totals, hipStream_t st,
                       uint32_t **w = nullptr, uint32_t **w2 = nullptr, bool w_is_position = false) {
     const bool few = cap <= kFewSort;
-    const int rows = (int)few_rows(cap);
+    const int rows = (int)few_rows(cap), nb = (int)radix_blocks(cap);
     for (int shift = 0; shift < bits; shift += kRadixBits) {
         // w_is_position: the second payload starts as each item's input position, generated by
         // the first pass instead of read
@@ -920,10 +932,12 @@ gsr_status radix_sort(uint32_t *&k, uint32_t *&v, uint32_t *&k2, uint32_t *&v2, 
             k_few_hist<<<rows, kFewThreads, 0, st>>>(k, n_dev, n_host, cap, shift, hist);
             const auto pass = cap <= kFewThreads * kFewRows * 4 ? k_few_pass<4> : k_few_pass<kFewItems>;
             pass<<<rows, kFewThreads, 0, st>>>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist);
-        } else if (radix_items(cap) == kShortItems)
-            radix_pass<kShortItems>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist, totals, st);
-        else
-            radix_pass<kRadixItems>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap, shift, hist, totals, st);
+        } else {
+            k_radix_hist<<<nb, kSortThreads, 0, st>>>(k, n_dev, n_host, cap, shift, nb, hist);
+            k_radix_scan_rows<<<kRadix, 256, 0, st>>>(hist, nb, totals, n_dev, n_host, cap);
+            k_radix_scatter<<<nb, kSortThreads, 0, st>>>(k, v, k2, v2, win, w ? *w2 : nullptr, n_dev, n_host, cap,
+                                                         shift, nb, hist, totals);
+        }
         uint32_t *tk = k, *tv = v;
         k = k2; v = v2; k2 = tk; v2 = tv;
         if (w) {
