@@ -14,11 +14,13 @@ __global__ void k_zero_f32(float *__restrict__ dst, int64_t n) {
 // Small pairs (at most kSmallPair records): each wave takes 64 consecutive visible pairs in
 // emission order.  Their records form one contiguous run, which the wave streams through LDS
 // kWinRecs records at a time with coalesced loads (a window that holds no record of a small pair
-// is not loaded), and each lane adds its own pair's records from there, in order.  With few pairs
-// (kFewPairs) that leaves SIMDs idle behind long chains, and a wave takes 16 pairs, four lanes each with
+// is not loaded), and each lane adds its own pair's records from there, in order.  With few pairs or long ones
+// that leaves SIMDs idle behind long chains, and a wave takes 16 pairs, four lanes each with
 // a part of the components (the order of every component's additions stays): 40k pairs with 600k
-// records 65 -> 18 us.  With 2.8M pairs the chip is full either way and the launch is bound by its
-// 0.8 GB (215 us).
+// records 65 -> 18 us.  The line lies in the pairs that are visible, which only the device knows: 200k pairs
+// of mixed sizes, 7 records on average, take 34 us so and 89 with a lane each, but 200k of 1 to 3 records 21 and 19,
+// and 1M of these 57 and 42.  Calls of more than kManyPairs pairs, visible or not, leave the choice out (it costs the
+// launch registers): with 2.8M the chip is full either way and the launch is bound by its 0.8 GB (215 us).
 // Large pairs (near Gaussians cover hundreds of tiles, and depth order puts them first): each is
 // summed by one whole wave, each lane striding over the records and a lane tree adding the 64
 // partial sums.  The large pairs are dealt out across the grid: lane l of wave w looks at pair
@@ -27,7 +29,7 @@ __global__ void k_zero_f32(float *__restrict__ dst, int64_t n) {
 // data, so the result repeats exactly.
 constexpr uint32_t kSmallPair = 64;
 constexpr int kPairWaves = 4;  // waves per workgroup
-constexpr int64_t kFewPairs = 1 << 20;  // (view, Gaussian) pairs, visible or not
+constexpr uint32_t kFewPairs = 1 << 18, kManyPairs = 1 << 20;
 constexpr int kWinRecs = 256;  // records per LDS window of a wave
 
 __device__ __forceinline__ uint32_t pair_count(const uint32_t *__restrict__ pair_gid,
@@ -40,19 +42,13 @@ __device__ __forceinline__ uint32_t pair_count(const uint32_t *__restrict__ pair
 
 // LPP: lanes per small pair (1 or 4)
 template <int LPP>
-__global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__restrict__ dinst,
-                                                                const uint32_t *__restrict__ pair_gid,
-                                                                const uint32_t *__restrict__ pair_first,
-                                                                const uint32_t *__restrict__ n_pairs,
-                                                                const uint32_t *__restrict__ ntiles,
-                                                                float *__restrict__ dsplat) {
-    // one window of records per wave: floats 0-3, 4-7 and 8-9 of each record, as float4
-    __shared__ float4 s_w4[kPairWaves][3][kWinRecs];
-    const uint32_t np = *n_pairs;
+__device__ __forceinline__ void pair_sums(const float *__restrict__ dinst, const uint32_t *__restrict__ pair_gid,
+                                          const uint32_t *__restrict__ pair_first, uint32_t np,
+                                          const uint32_t *__restrict__ ntiles, float *__restrict__ dsplat,
+                                          float4 (*const win)[kWinRecs]) {
     const int lane = __lane_id();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    float4(*const win)[kWinRecs] = s_w4[threadIdx.x >> 6];
     // small pairs, one per lane
     constexpr uint32_t kPer = 64 / LPP;
     constexpr int kParts = LPP == 1 ? 3 : 1;  // float4 parts of a record per lane
@@ -159,6 +155,23 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__r
     }
 }
 
+// FEW: four lanes per pair where few pairs are visible
+template <bool FEW>
+__global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__restrict__ dinst,
+                                                                const uint32_t *__restrict__ pair_gid,
+                                                                const uint32_t *__restrict__ pair_first,
+                                                                const uint32_t *__restrict__ n_pairs,
+                                                                const uint32_t *__restrict__ ntiles,
+                                                                float *__restrict__ dsplat) {
+    // one window of records per wave: floats 0-3, 4-7 and 8-9 of each record, as float4
+    __shared__ float4 s_w4[kPairWaves][3][kWinRecs];
+    const uint32_t np = *n_pairs;
+    if (FEW && np <= kFewPairs)
+        pair_sums<4>(dinst, pair_gid, pair_first, np, ntiles, dsplat, s_w4[threadIdx.x >> 6]);
+    else
+        pair_sums<1>(dinst, pair_gid, pair_first, np, ntiles, dsplat, s_w4[threadIdx.x >> 6]);
+}
+
 }  // namespace gsr
 
 using namespace gsr;
@@ -172,11 +185,13 @@ extern "C" gsr_status gsr_pair_grads_launch(const float *dinst, const gsr_emissi
         const int nz = (int)(ceil_div(words, 256) < 16384 ? ceil_div(words, 256) : 16384);
         k_zero_f32<<<nz, 256, 0, st>>>(dsplat, words);
     }
-    const bool few = VN <= kFewPairs;
-    const int64_t want = ceil_div(VN, (few ? 16 : 64) * kPairWaves);
-    const int nb = (int)(want < 8192 ? want : 8192);
-    const auto kernel = few ? k_pair_grads<4> : k_pair_grads<1>;
-    kernel<<<nb, 64 * kPairWaves, 0, st>>>(dinst, em->pair_gid, em->pair_first, em->n_pairs, tile_info, dsplat);
+    // enough workgroups for either form; idle ones are not free (a CU holds three)
+    const bool choose = VN <= (int64_t)kManyPairs;
+    const int64_t few = choose ? ceil_div(VN < (int64_t)kFewPairs ? VN : (int64_t)kFewPairs, 16 * kPairWaves) : 0;
+    const int64_t all = ceil_div(VN, 64 * kPairWaves), want = all > few ? all : few;
+    const auto kernel = choose ? k_pair_grads<true> : k_pair_grads<false>;
+    kernel<<<(int)(want < 8192 ? want : 8192), 64 * kPairWaves, 0, st>>>(dinst, em->pair_gid, em->pair_first,
+                                                                        em->n_pairs, tile_info, dsplat);
     return last_launch();
 }
 
