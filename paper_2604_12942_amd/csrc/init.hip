@@ -579,6 +579,9 @@ __device__ __forceinline__ uint8_t voxel_init(const gsr_voxels &V, const float *
 // the segment counts 39 (228).
 // The count only says how many voxels the table holds: a point of a voxel past it takes the per-point form,
 // so the results do not depend on it.
+// Its two launches take 5 us, so small clouds go without: the whole call takes 40 us without and 43 with it at
+// 100k points with a model's predictions, 56 and 52 at 200k, and without predictions 61 either way at 200k and 82 and 78 at 500k.
+constexpr int64_t kTableFrom = 1 << 17;  // points, twice as many without predictions
 struct CascadeTable {
     VoxInit *rec;  // null: no table (no count, or the sh output overlaps an input or is not 16-byte aligned)
     int64_t floats;  // of the sh output
@@ -762,14 +765,15 @@ extern "C" gsr_status gsr_cascade_launch(const float *pts, const float *col, con
     if (s != GSR_OK) return s;
     const int g = grid(n), K = (sh_degree + 1) * (sh_degree + 1);
     // the sh output holds the voxel table until it is written, unless it shares memory with something
-    // read or written before that (a caller may convert colours in place) or the caller gives no voxel count
+    // read or written before that (a caller may convert colours in place), the cloud is small, or the caller
+    // gives no voxel count
     CascadeTable T{reinterpret_cast<VoxInit *>(out->sh), 3 * (int64_t)K * n};
     const uintptr_t lo = reinterpret_cast<uintptr_t>(out->sh), hi = lo + (uintptr_t)T.floats * 4;
     auto clash = [&](const void *p, int64_t bytes) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(p);
         return p && a < hi && a + (uintptr_t)bytes > lo;
     };
-    if (!vox->n_voxels || (lo & 15) || clash(pts, 12 * n) || clash(col, 12 * n) || clash(depth, 4 * n) || clash(seg, 4 * n) ||
+    if (n < (pred ? kTableFrom : 2 * kTableFrom) || !vox->n_voxels || (lo & 15) || clash(pts, 12 * n) || clash(col, 12 * n) || clash(depth, 4 * n) || clash(seg, 4 * n) ||
         clash(pred, 32 * n) || clash(vox->point_voxel, 4 * n) || clash(vox->reliable, n) || clash(vox->s_pca, 12 * n) ||
         clash(vox->R, 36 * n) || clash(vox->n_voxels, 4) || clash(out->means, 12 * n) || clash(out->log_scales, 12 * n) ||
         clash(out->quats, 16 * n) || clash(out->opacity_logits, 4 * n) || clash(branch, n) || clash(ws, gsr_cascade_ws_bytes(nseg)))

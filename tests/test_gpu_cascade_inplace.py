@@ -11,11 +11,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("sh_degree", [0, 1])
 @pytest.mark.parametrize("name", ["log_scales", "quats", "sh"])
-def test_colours_in_place_of_an_output(name, sh_degree):
+@pytest.mark.parametrize("nv", [3000, 24_000])  # without and with room for the table of voxel records
+def test_colours_in_place_of_an_output(name, sh_degree, nv):
     import paper_2604_12942_amd as gsr
     from paper_2604_12942_amd import _abi
     rng = np.random.default_rng(7)
-    nv, per = 3000, 12
+    per = 12
     n = nv * per
     c = np.arange(nv).repeat(per)
     base = np.stack([c % 20, (c // 20) % 20, c // 400], 1) * 0.5
