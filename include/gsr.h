@@ -671,8 +671,12 @@ GSR_API gsr_status gsr_pointnet_fwd(const float *points, int64_t n, const gsr_vo
  * Sigma_pred = R(q / |q|) diag(exp(2 s)) R(q / |q|)^T, targets cov_t [6][n] = (xx, xy, xz, yy, yz, zz)
  * and o_t [n].  The backward GEMMs round their inputs (upstream gradients included) to BF16; the
  * max-pool routes to the argmax row (lowest row on ties).  The loss value is ADDED to *loss
- * (device float64).  blocks: persistent workgroups (each keeps partial sums, reduced in a fixed
- * order); ws: gsr_pointnet_bwd_workspace(blocks) bytes. */
+ * (device float64).  blocks: an upper bound of the persistent workgroups (at most one per compute
+ * unit is launched; each keeps partial sums, reduced in a fixed order, the weights' in float64).  The
+ * biases are summed in float32, in a fixed order by waves, if the workspace rows of the workgroups
+ * not launched have room for the waves' sums (blocks some 15 % above the workgroups launched), else
+ * like the weights: their rounding depends on blocks and the number of compute units.
+ * ws: gsr_pointnet_bwd_workspace(blocks) bytes. */
 GSR_API size_t gsr_pointnet_bwd_workspace(int32_t blocks);
 GSR_API gsr_status gsr_pointnet_bwd(const float *points, int64_t n, const gsr_voxels *vox, const float *weights,
                                     const float *cov_t, const float *o_t, const uint8_t *tmask, float inv_count,

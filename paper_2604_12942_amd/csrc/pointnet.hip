@@ -895,10 +895,11 @@ __global__ __launch_bounds__(64 * kBW) __attribute__((amdgpu_waves_per_eu(2, 2))
 // Fixed-order sums of the partial gradients.  Blocks below kReduceBlocks: 64 weights each over the nb
 // workgroups' rows, four lanes per weight so that several loads are in flight everywhere (one lane per
 // weight over 512 rows took 120 us; this takes 5, 13 with the biases).  With bias_part, the blocks above take 8 biases
-// each, in the order in which `blocks` workgroups of one eight-voxel tile at a time would have summed
-// them (tile t belongs to share t mod blocks; shares add up one after another in FP32): the biases
-// enter every activation unrounded, and a training run then steps through the same biases however
-// the tiles are spread over the chip.
+// each, in FP32: wave k's sum (of tiles k, k + 8 nb, ... of eight voxels, in that order) belongs to share k mod
+// `blocks`, a share adds its waves in order, and the shares add up one after another.  While no wave takes a second
+// tile (64 voxels a workgroup: 16,384 on 256 CUs) that is the order in which `blocks` workgroups of one tile at a
+// time would have summed them: the biases enter every activation unrounded, and a training run on such a scene
+// steps through the same biases whatever the number of CUs.  Beyond, the order is fixed for a number of CUs and `blocks`.
 static_assert(kNB % 8 == 0, "whole blocks of biases");
 constexpr int kReduceBlocks = (kNW + 63) / 64, kShares = 512, kShareCols = 8;
 __global__ __launch_bounds__(256) void k_pn_reduce(const float *__restrict__ part, int nb,
