@@ -19,7 +19,12 @@ __global__ void k_zero_f32(float *__restrict__ dst, int64_t n) {
 // a part of the components (the order of every component's additions stays): 40k pairs with 600k
 // records 65 -> 18 us.  The line lies in the pairs that are visible, which only the device knows: 200k pairs
 // of mixed sizes, 7 records on average, take 34 us so and 89 with a lane each, but 200k of 1 to 3 records 21 and 19,
-// and 1M of these 57 and 42.  Calls of more than kManyPairs pairs, visible or not, leave the choice out (it costs the
+// and 1M of these 57 and 42.  Above kFewPairs it lies in the front of the list as well: pairs are listed by depth, the near
+// ones are long, and the waves that hold these are the chain that the others wait for (up to 64 pairs of 64 records).  A map
+// of 637k Gaussians seen at 1058 x 1020 on 8x32 tiles has 375k pairs of 3.7 records, 39 in the first 64th: 41 us with four
+// lanes, 91 with one; 569k pairs of 4.8, 62 in front: 58 and 114; 500k of 2, 5 and 12 records all through: 40, 47 and
+// 61 with four and 31, 38 and 60 with one, so the line lies at kLongFront records per pair of the first 64th.
+// Calls of more than kManyPairs pairs, visible or not, leave the choice out (it costs the
 // launch registers): with 2.8M the chip is full either way and the launch is bound by its 0.8 GB (215 us).
 // Large pairs (near Gaussians cover hundreds of tiles, and depth order puts them first): each is
 // summed by one whole wave, each lane striding over the records and a lane tree adding the 64
@@ -29,7 +34,7 @@ __global__ void k_zero_f32(float *__restrict__ dst, int64_t n) {
 // data, so the result repeats exactly.
 constexpr uint32_t kSmallPair = 64;
 constexpr int kPairWaves = 4;  // waves per workgroup
-constexpr uint32_t kFewPairs = 1 << 18, kManyPairs = 1 << 20;
+constexpr uint32_t kFewPairs = 1 << 18, kManyPairs = 1 << 20, kLongFront = 16;
 constexpr int kWinRecs = 256;  // records per LDS window of a wave
 
 __device__ __forceinline__ uint32_t pair_count(const uint32_t *__restrict__ pair_gid,
@@ -155,7 +160,7 @@ __device__ __forceinline__ void pair_sums(const float *__restrict__ dinst, const
     }
 }
 
-// FEW: four lanes per pair where few pairs are visible
+// FEW: four lanes per pair where few pairs are visible or those in front are long
 template <bool FEW>
 __global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__restrict__ dinst,
                                                                 const uint32_t *__restrict__ pair_gid,
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair_grads(const float *__r
     // one window of records per wave: floats 0-3, 4-7 and 8-9 of each record, as float4
     __shared__ float4 s_w4[kPairWaves][3][kWinRecs];
     const uint32_t np = *n_pairs;
-    if (FEW && np <= kFewPairs)
+    if (FEW && (np <= kFewPairs || pair_first[np / 64] >= kLongFront * (np / 64)))
         pair_sums<4>(dinst, pair_gid, pair_first, np, ntiles, dsplat, s_w4[threadIdx.x >> 6]);
     else
         pair_sums<1>(dinst, pair_gid, pair_first, np, ntiles, dsplat, s_w4[threadIdx.x >> 6]);
