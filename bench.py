@@ -27,9 +27,9 @@ import synth  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 157.3
-# without packed FP32 (the library is compiled without packed FP32 instructions):
-# 256 CU x 4 SIMD x 16 lanes x 2 (FMA) x 2.4 GHz
-FP32_PEAK_NONPACKED_TFLOPS = 78.6
+# what non-packed v_fmac_f32 reaches (the library is compiled without packed FP32 instructions): 1,096 G wave
+# instructions/s x 64 lanes x 2, measured with eight waves per SIMD and eight independent chains each
+FP32_PEAK_NONPACKED_TFLOPS = 140.3
 # algorithmic float operations per composited (pixel, Gaussian) pair, plus one exp each (not
 # counted): forward 20, backward 45 (the fused step does both)
 FLOP_PER_BLEND_FWD = 20
@@ -43,7 +43,7 @@ KERNEL_OF_STAGE = dict(project="k_project", bin_sort="gsr_bin_sort (12 kernels)"
 # workload, each scaled by the counter's reading for a 256 MiB device copy (fetch x1.9997, write x1.0);
 # keyed by (kernel, tile), with the SHA-256 prefix of the kernel's sources at measurement time: a
 # figure whose sources have changed since is reported as null.
-TRAFFIC = {("k_render_bwd_l1", "8x32"): (2914947201, "37f55fef502d2a0d")}
+TRAFFIC = {("k_render_bwd_l1", "8x32"): (2915947304, "0837ed1781a5c5ba")}
 KERNEL_SOURCES = {"k_render_bwd_l1": ["csrc/gsr_internal.h", "csrc/render.hip"],
                   "k_render_fwd": ["csrc/gsr_internal.h", "csrc/render.hip"],
                   "k_project_bwd": ["csrc/gsr_internal.h", "csrc/project.hip"]}

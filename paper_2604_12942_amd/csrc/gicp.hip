@@ -402,7 +402,7 @@ __device__ __forceinline__ void gicp_pair_sums(uint32_t bi, int64_t j, const flo
 
 // One Gauss-Newton iteration.  Each block takes chunks of 64 sources: four passes of sixteen
 // sixteen-lane searches, then its first wave linearises the 64 pairs.  The per-block sums go to
-// partial[e][block]; the last of the active blocks adds them and updates the pose.
+// partial[e][block]; k_gicp_solve, a launch of its own, adds them and updates the pose.
 //
 // The search is bound by the latency of its dependent loads, not by bytes or FLOPs.  One lane per
 // source walked 27 cells and every candidate in them one after another, 1.1 waves per SIMD, in 1.46
